@@ -312,6 +312,12 @@ int pbi_mixed_begin(pb_problem* pb)
     return PB_OK;
 }
 
+// whether the read-back takes the sums over cut points by box expansions, within `bytes`
+bool pbi_tree_plan(const pb_problem* pb, size_t bytes, TreePlan* out)
+{
+    return pb->na > 0 && tree_plan(pb->g, pbi_atoms(pb), pb->alo, pb->ahi, pb->rmax, pb->ncut, bytes, out);
+}
+
 // energy read-back: kernels and the read-back of the sums (and, with finish_mixed, the final
 // reliable update and the CG state) behind pb->ev; pbi_energy_end collects after the event
 int pbi_energy_begin(pb_problem* pb, int finish_mixed)
@@ -346,15 +352,24 @@ int pbi_energy_begin(pb_problem* pb, int finish_mixed)
         HIPCHK(launch_ru_fin(s, pb->st, pb->part_res, pb->nbres, 0, 0.0, 0.0));
     }
     const Atoms at = pbi_atoms(pb);
+    // the sums over cut points by box expansions where those are the better way, in the work
+    // space that the direct sum's partials would take
+    TreePlan tree;
+    const int* pos = nullptr;
+    const bool by_tree = pbi_tree_plan(pb, sizeof(double) * (size_t)energy_partial_doubles((int)na1, pb->e_nchunk), &tree);
+    if (by_tree) HIPCHK(launch_tree_order(s, tree, at, pb->cutkey, pb->e_tmp[0], &pos));
     HIPCHK(launch_fill(s, pb->e_tmp[3], 16 * sizeof(double)));
     HIPCHK(launch_edge_fields(s, pb->g, at, pb->prm.eps_in, pb->prm.eps_out, pb->ncut, pb->cutkey, pb->code, pb->alpha,
-                              pb->kcut, pb->x, pb->gb, pb->wp, pb->F, pb->phip, pb->pts, pb->rp, pb->np));
+                              pb->kcut, pb->x, pb->gb, pb->wp, pb->F, pb->phip, pb->pts, pb->rp, pb->np, pos));
     pb->prof_nbody_ms = pb->prof_nbody_pairs = 0;
-    pb->nb_timed = pb->ctx->profile && pb->na > 0 && pb->ncut > 0;
+    pb->nb_timed = pb->ctx->profile && pb->na > 0 && pb->ncut > 0 && !by_tree;
     if (pb->nb_timed && !pb->nb_ev[0])
         for (int e = 0; e < 2; ++e) HIPCHK(hipEventCreateWithFlags(&pb->nb_ev[e], hipEventDisableSystemFence));
     if (pb->na > 0) {
-        if (pb->ncut > 0) {
+        if (by_tree) {
+            HIPCHK(launch_tree_sums(s, tree, pb->pts, pb->e_tmp[0]));
+            pb->e_nchunk = tree_chunks(tree);
+        } else if (pb->ncut > 0) {
             if (pb->nb_timed) HIPCHK(hipEventRecord(pb->nb_ev[0], s));
             HIPCHK(launch_nbody(s, at, pb->ncut, pb->pts, pb->e_tmp[0], pb->e_nchunk));
             if (pb->nb_timed) HIPCHK(hipEventRecord(pb->nb_ev[1], s));
@@ -706,7 +721,12 @@ int build_begin(pb_ctx* ctx, const pb_params* prm, int64_t na, const double* xyz
     }
     HK(hipMemcpyAsync(pb->xyzr, hx, sizeof(double) * 4 * na1, hipMemcpyHostToDevice, s));
     HK(hipMemcpyAsync(pb->q, hq, sizeof(double) * na1, hipMemcpyHostToDevice, s));
-    for (int d = 0; d < 3; ++d) pb->ctr[d] = na > 0 ? 0.5 * (lo[d] + hi[d]) : 0.0;
+    for (int d = 0; d < 3; ++d) {
+        pb->ctr[d] = na > 0 ? 0.5 * (lo[d] + hi[d]) : 0.0;
+        pb->alo[d] = lo[d];
+        pb->ahi[d] = hi[d];
+    }
+    pb->rmax = rmax;
     const Atoms at = pbi_atoms(pb);
 
     // bins of edge >= R_max + h (and >= 2h) so that the 27 bins around a node or an edge end

@@ -46,12 +46,14 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double* sh, int
     }
 }
 
+template <bool kPlaced>
 __global__ void __launch_bounds__(256) k_edge_fields(Grid g, Atoms at, double eps_in, double eps_out, int64_t ncut,
                                                      const int64_t* cutkey, const uint32_t* code,
                                                      const double* alpha, const double* kcut,
                                                      const double* x, const double* gb, const double* wp,
                                                      double* F, double* phip, double* pts,
-                                                     const double* rp, const double* np)
+                                                     const double* rp, const double* np,
+                                                     const int* __restrict__ pos)
 {
     int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (c >= ncut) return;
@@ -70,32 +72,23 @@ __global__ void __launch_bounds__(256) k_edge_fields(Grid g, Atoms at, double ep
     (void)kcut;
     F[c] = f;
     phip[c] = pp;
-    double* o = pts + CUT_POINT_DOUBLES * c;
+    // one record per cut point, or, at the places given, one array per component
+    double* o = kPlaced ? pts + pos[c] : pts + CUT_POINT_DOUBLES * c;
+    const int64_t n = kPlaced ? ncut : 1;
     // relative to the atoms' centre, as the N-body kernel takes the atoms
     const double px = rp[3 * c] - at.cx, py = rp[3 * c + 1] - at.cy, pz = rp[3 * c + 2] - at.cz;
     const double wphi = wp[c] * pp;
     const double ux = wphi * np[3 * c], uy = wphi * np[3 * c + 1], uz = wphi * np[3 * c + 2];
     o[0] = px;
-    o[1] = py;
-    o[2] = pz;
-    o[3] = ux;
-    o[4] = uy;
-    o[5] = uz;
-    o[6] = f;
-    o[7] = fma(px, px, fma(py, py, pz * pz));
-    o[8] = 2.0 * fma(px, ux, fma(py, uy, pz * uz));
-    o[9] = 0.0;
-}
-
-// 1/sqrt(x) for the N-body sum: the hardware FP64 estimate y (relative error up to about
-// 5.2e-8) and one Newton step y + y e / 2, e = 1 - x y^2.  The step leaves 3e^2/8, under 4e-15
-// relative and of one sign, below the rounding of the read-back's sums over millions of cut
-// points (about 1e-13 relative); four operations where rsqrt_fp64's series step takes five.
-__device__ __forceinline__ double rsqrt_nb(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x, y * y, 1.0);
-    return fma(0.5 * y, e, y);
+    o[n] = py;
+    o[2 * n] = pz;
+    o[3 * n] = ux;
+    o[4 * n] = uy;
+    o[5 * n] = uz;
+    o[6 * n] = f;
+    o[7 * n] = fma(px, px, fma(py, py, pz * pz));
+    o[8 * n] = 2.0 * fma(px, ux, fma(py, uy, pz * uz));
+    if (!kPlaced) o[9] = 0.0;
 }
 
 constexpr int NB_ATOMS = 4;                       // atoms per thread
@@ -345,11 +338,16 @@ int nbody_chunks(int n_atoms, int64_t ncut)
 hipError_t launch_edge_fields(hipStream_t s, const Grid& g, const Atoms& at, double eps_in, double eps_out, int64_t ncut,
                               const int64_t* cutkey, const uint32_t* code, const double* alpha,
                               const double* kcut, const double* x, const double* gb, const double* wp,
-                              double* F, double* phip, double* pts, const double* rp, const double* np)
+                              double* F, double* phip, double* pts, const double* rp, const double* np,
+                              const int* pos)
 {
     if (ncut == 0) return hipSuccess;
-    k_edge_fields<<<nblk(ncut, 256), 256, 0, s>>>(g, at, eps_in, eps_out, ncut, cutkey, code, alpha, kcut, x, gb,
-                                                   wp, F, phip, pts, rp, np);
+    if (pos)
+        k_edge_fields<true><<<nblk(ncut, 256), 256, 0, s>>>(g, at, eps_in, eps_out, ncut, cutkey, code, alpha, kcut, x,
+                                                            gb, wp, F, phip, pts, rp, np, pos);
+    else
+        k_edge_fields<false><<<nblk(ncut, 256), 256, 0, s>>>(g, at, eps_in, eps_out, ncut, cutkey, code, alpha, kcut,
+                                                             x, gb, wp, F, phip, pts, rp, np, nullptr);
     return hipGetLastError();
 }
 

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "pb_internal.h"
+#include "pb_tree.h"
 
 int pbi_fail(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 
@@ -201,6 +202,7 @@ struct pb_problem {
     pbk::Coef cf;
     double lB, kD;
     double ctr[3] = {0.0, 0.0, 0.0};   // centre of the atoms' bounding box (Atoms::cx, cy, cz)
+    double alo[3] = {0.0, 0.0, 0.0}, ahi[3] = {0.0, 0.0, 0.0}, rmax = 0.0;   // that box and the largest radius
     DevAlloc mem;
     // inputs
     double* xyzr = nullptr;
@@ -263,6 +265,7 @@ int64_t pbi_build_counted_cuts(const pb_problem* pb);
 int pbi_event_done(pb_problem* pb);
 void pbi_problem_destroy(pb_problem* pb, bool sync);   // sync=false: its event has completed
 int pbi_energy_begin(pb_problem* pb, int finish_mixed);            // kernels + read-back
+bool pbi_tree_plan(const pb_problem* pb, size_t bytes, pbk::TreePlan* out);
 // take the device address of the allocation-free read-back's scratch array on `device` (the
 // current device), once per device (pb_noalloc.hip)
 int pbi_scratch_setup(int device);

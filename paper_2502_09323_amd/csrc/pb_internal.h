@@ -64,6 +64,17 @@ __device__ __forceinline__ double rsqrt_fp64(double x)
     return fma(y, e * fma(e, 0.375, 0.5), y);
 }
 
+// 1/sqrt(x) for the N-body sum: the hardware FP64 estimate y (relative error up to about
+// 5.2e-8) and one Newton step y + y e / 2, e = 1 - x y^2.  The step leaves 3e^2/8, under 4e-15
+// relative and of one sign, below the rounding of the read-back's sums over millions of cut
+// points (about 1e-13 relative); four operations where rsqrt_fp64's series step takes five.
+__device__ __forceinline__ double rsqrt_nb(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x, y * y, 1.0);
+    return fma(0.5 * y, e, y);
+}
+
 struct Atoms {
     int n;
     const double* xyzr;  // 4 per atom: x, y, z, radius
@@ -253,7 +264,7 @@ hipError_t launch_edge_fields(hipStream_t s, const Grid& g, const Atoms& at, dou
                               const double* alpha, const double* kcut, const double* x,
                               const double* gb, const double* wp, double* F, double* phip,
                               double* pts /* CUT_POINT_DOUBLES per cut point */, const double* rp,
-                              const double* np);
+                              const double* np, const int* pos /* place of each cut point in pts; null: its own */);
 hipError_t launch_nbody(hipStream_t s, const Atoms& at, int64_t ncut, const double* pts,
                         double* partial, int nchunk);
 // phic: n_atoms * ncc partial Coulomb potentials, ncc = coulomb_chunks(n_atoms)

@@ -114,12 +114,19 @@ int pb_energy_noalloc(pb_problem* pb, pb_energy_out* out, double* phi_reac)
     double* sums = (double*)(b + L.sums);
     hipStream_t s = pb->ctx->stream;
     const Atoms at = pbi_atoms(pb);
+    TreePlan tree;
+    const int* pos = nullptr;
+    const bool by_tree = pbi_tree_plan(pb, 8 * (size_t)energy_partial_doubles(na1, nchunk), &tree);
     hipError_t e = launch_fill(s, sums, 16 * sizeof(double));
+    if (e == hipSuccess && by_tree) e = launch_tree_order(s, tree, at, pb->cutkey, partial, &pos);
     if (e == hipSuccess)
         e = launch_edge_fields(s, pb->g, at, pb->prm.eps_in, pb->prm.eps_out, ncut, pb->cutkey, pb->code, pb->alpha,
-                               pb->kcut, pb->x, pb->gb, pb->wp, F, phip, pts, pb->rp, pb->np);
+                               pb->kcut, pb->x, pb->gb, pb->wp, F, phip, pts, pb->rp, pb->np, pos);
     if (e == hipSuccess && na > 0) {
-        if (ncut > 0)
+        if (by_tree) {
+            e = launch_tree_sums(s, tree, pts, partial);
+            nchunk = tree_chunks(tree);
+        } else if (ncut > 0)
             e = launch_nbody(s, at, ncut, pts, partial, nchunk);
         else
             e = launch_fill(s, partial, sizeof(double) * 2 * (size_t)na1 * (size_t)nchunk);
