@@ -845,10 +845,14 @@ int pbi_build_continue(pb_problem* pb)
     HIPCHK(launch_fill(s, pb->gb, sizeof(double) * N));
     HIPCHK(launch_fill(s, pb->x, sizeof(double) * N));
     if (prm->bc == PB_BC_DH && pb->na > 0) {
-        const DhSplit sp = dh_split(g, at.n);
+        DhInterp in;
+        const bool interp = prm->precision == PB_MIXED && dh_interp_plan(g, at, pb->alo, pb->ahi, pb->kD, &in);
+        const DhSplit sp = interp ? in.sp : dh_split(g, at.n);
         T.dhpart = dalloc<double>(pb, (size_t)sp.ranges * sp.nbox, &rc);
         CK(rc);
-        if (prm->precision == PB_MIXED)
+        if (interp)
+            HIPCHK(launch_bc_dh_interp(s, g, at, pb->kD, prm->eps_out, in, T.dhpart, pb->gb));
+        else if (prm->precision == PB_MIXED)
             HIPCHK(launch_bc_dh32(s, g, at, pb->kD, prm->eps_out, T.dhpart, pb->gb));
         else
             HIPCHK(launch_bc_dh(s, g, at, pb->kD, prm->eps_out, T.dhpart, pb->gb));

@@ -565,8 +565,8 @@ __device__ __forceinline__ double exp_dh(double r, const DhExp& E, const double*
 // block b % blocks of the faces and the atoms of range b / blocks (staged in LDS with the
 // face's own w term); its partial sums go to part[range][node] (the box-node numbering of
 // box_node), which k_bc_dh_sum adds up in range order.
-constexpr int DH_PU = 2, DH_PV = 4;
-constexpr int DH_GROUP = 32;   // atoms per FP32 partial sum of the mixed kernel   // nodes per thread along u, v
+constexpr int DH_PU = 2, DH_PV = 4;   // nodes per thread along u, v
+constexpr int DH_GROUP = 32;          // atoms per FP32 partial sum of the mixed kernel
 
 // a thread's patch of box-face nodes: its face (normal axis w, in-plane axes ua slower and va
 // faster), the patch's first node (u0, v0) on the face's U x V array, and the coordinates,
@@ -578,7 +578,16 @@ struct DhPatch {
     double pw, pu[DH_PU], pv[DH_PV];
 };
 
-__device__ __forceinline__ DhPatch dh_patch(const Grid& g, const Atoms& at, const DhFaces& fc, int tile)
+// coordinate, relative to the atoms' centre, of sample s along axis a (0: u, 1: v) of face f
+__device__ __forceinline__ double dh_sample(const DhPanels& pn, int f, int a, int s)
+{
+    const int n = pn.n[f][a], p = s / n, j = s - p * n;
+    return fma(pn.half[f][a], (double)(2 * p + 1) + cospi((double)(2 * j + 1) / (double)(2 * n)), pn.lo[f][a]);
+}
+
+// the patch's coordinates are those of box nodes, or of the samples of a face (kSamples)
+template <bool kSamples>
+__device__ __forceinline__ DhPatch dh_patch(const Grid& g, const Atoms& at, const DhFaces& fc, const DhPanels& pn, int tile)
 {
     DhPatch P;
     P.f = 0;
@@ -598,9 +607,15 @@ __device__ __forceinline__ DhPatch dh_patch(const Grid& g, const Atoms& at, cons
     const int nn[3] = {g.nx, g.ny, g.nz};
     P.pw = node_x(g, P.w, (P.f & 1) ? nn[P.w] - 1 : 0) - cen[P.w];
 #pragma unroll
-    for (int a = 0; a < DH_PU; ++a) P.pu[a] = node_x(g, P.ua, min(P.u0 + a, P.U - 1) + ushift) - cen[P.ua];
+    for (int a = 0; a < DH_PU; ++a) {
+        const int u = min(P.u0 + a, P.U - 1);
+        P.pu[a] = kSamples ? dh_sample(pn, P.f, 0, u) : node_x(g, P.ua, u + ushift) - cen[P.ua];
+    }
 #pragma unroll
-    for (int b = 0; b < DH_PV; ++b) P.pv[b] = node_x(g, P.va, min(P.v0 + b, P.V - 1) + vshift) - cen[P.va];
+    for (int b = 0; b < DH_PV; ++b) {
+        const int v = min(P.v0 + b, P.V - 1);
+        P.pv[b] = kSamples ? dh_sample(pn, P.f, 1, v) : node_x(g, P.va, v + vshift) - cen[P.va];
+    }
     return P;
 }
 
@@ -641,13 +656,14 @@ __device__ __forceinline__ void dh_write(const DhPatch& P, const DhFaces& fc, co
                 part[(int64_t)rg * sp.nbox + fc.base[P.f] + (int64_t)(P.u0 + a) * P.V + (P.v0 + b)] = s[a][b];
 }
 
-__global__ void __launch_bounds__(256) k_bc_dh(Grid g, Atoms at, DhExp E, DhSplit sp, DhFaces fc, double* part)
+template <bool kSamples>
+__global__ void __launch_bounds__(256) k_bc_dh(Grid g, Atoms at, DhExp E, DhSplit sp, DhFaces fc, DhPanels pn, double* part)
 {
     __shared__ double sa[256 * 4];
     __shared__ double T[kDhTable];
     for (int j = threadIdx.x; j < kDhTable; j += 256) T[j] = exp2((double)j / kDhTable);
     const int tile = (int)(blockIdx.x % fc.tile0[6]), rg = (int)(blockIdx.x / fc.tile0[6]);
-    const DhPatch P = dh_patch(g, at, fc, tile);
+    const DhPatch P = dh_patch<kSamples>(g, at, fc, pn, tile);
     double s[DH_PU][DH_PV];
 #pragma unroll
     for (int a = 0; a < DH_PU; ++a)
@@ -709,7 +725,7 @@ __global__ void __launch_bounds__(256) k_bc_dh32(Grid g, Atoms at, double kD, Dh
     __shared__ double sa[256 * 3];
     __shared__ float sq[256];
     const int tile = (int)(blockIdx.x % fc.tile0[6]), rg = (int)(blockIdx.x / fc.tile0[6]);
-    const DhPatch P = dh_patch(g, at, fc, tile);
+    const DhPatch P = dh_patch<false>(g, at, fc, DhPanels{}, tile);
     const float mk = (float)(-kD * 1.4426950408889634);   // -kD log2(e)
     double s[DH_PU][DH_PV];
 #pragma unroll
@@ -773,6 +789,114 @@ __global__ void __launch_bounds__(256) k_bc_dh_sum(Grid g, DhSplit sp, const dou
     int i, j, k;
     box_node(g, t, i, j, k);
     gb[g.idx(i, j, k)] = s / eps_out;
+}
+
+// ---- box values by interpolation ------------------------------------------------------------
+// All atoms lie at least D from a face's plane, so the box value is an analytic function on the
+// face: a panel of half-length a, sampled at the n Chebyshev nodes of each axis, is interpolated
+// with an error of rho^-n, rho = D/a + sqrt((D/a)^2 + 1) (the nearest singularity lies D off the
+// plane).  What is interpolated is the value divided by exp(-kD r)/r of one charge at the atoms'
+// centre, which is flat where the value itself falls by orders of magnitude across a face.
+//
+// The mixed form's values come from samples that are FP64 sums (k_bc_dh), so they are closer to the
+// exact ones than the FP32 sums at every node that they replace: off by 3e-14 of the absolute-value
+// scale and less, against 1e-8 to 1e-7.  385^3, 60,000 atoms: 32,000 samples for 887,000 nodes, 2.4
+// ms in place of 15.2 (with FP32 sums at the samples 1.1 ms, but off by up to 1.5 times what the
+// nodes' own sums were).  The FP64 form keeps its sums at every node.
+
+// exp(-kD r) / r of a unit charge at the atoms' centre
+__device__ __forceinline__ double dh_centre(double kD, double w, double u, double v)
+{
+    const double r = sqrt(fma(w, w, fma(u, u, v * v)));
+    return exp(-kD * r) / r;
+}
+
+// the samples from the partial sums of the atom ranges, added in range order, over the value of a
+// charge at the centre; in place of the first range's
+__global__ void __launch_bounds__(256) k_dh_samples(Grid g, Atoms at, DhSplit sp, DhFaces fc, DhPanels pn, double kD,
+                                                    double eps_out, double* part)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= sp.nbox) return;
+    double s = 0.0;
+    for (int r = 0; r < sp.ranges; ++r) s += part[(int64_t)r * sp.nbox + t];
+    int f = 0;
+    while (f < 5 && t >= fc.base[f + 1]) ++f;
+    const int e = (int)(t - fc.base[f]), w = f >> 1;
+    const double cen[3] = {at.cx, at.cy, at.cz};
+    const int nn[3] = {g.nx, g.ny, g.nz};
+    const double pw = node_x(g, w, (f & 1) ? nn[w] - 1 : 0) - cen[w];
+    const double c = dh_centre(kD, pw, dh_sample(pn, f, 0, e / fc.V[f]), dh_sample(pn, f, 1, e % fc.V[f]));
+    part[t] = s / (eps_out * c);
+}
+
+// Box nodes of one face row (fixed u) per block: the row's weights along u collapse the samples to
+// one row of them, from which each thread interpolates its nodes along v (barycentric form).  Per
+// node about n divisions and multiply-adds: a few microseconds beside the sums they replace.
+__global__ void __launch_bounds__(256) k_dh_interp(Grid g, Atoms at, DhFaces fc, DhPanels pn, double kD,
+                                                   const double* __restrict__ smp, double* __restrict__ gb)
+{
+    __shared__ double Lu[kDhMaxDegree], xs[kDhMaxDegree], ws[kDhMaxDegree], H[kDhMaxRow];
+    int f = 0, u = (int)blockIdx.x;
+    while (f < 5 && u >= pn.nodes[f][0]) u -= pn.nodes[f++][0];
+    const int w = f >> 1, ua = w == 0 ? 1 : 0, va = w == 2 ? 1 : 2;
+    const int ushift = w == 0 ? 0 : 1, vshift = w == 2 ? 1 : 0;
+    const double cen[3] = {at.cx, at.cy, at.cz};
+    const int nn[3] = {g.nx, g.ny, g.nz}, side = (f & 1) ? nn[w] - 1 : 0;
+    const double pw = node_x(g, w, side) - cen[w], pu = node_x(g, ua, u + ushift) - cen[ua];
+    const int nu = pn.n[f][0], nv = pn.n[f][1], V = fc.V[f];
+    // the panel of coordinate x along axis a, and x on the panel's [-1, 1]
+    auto panel = [&](int a, double x, double& y) {
+        const double q = (x - pn.lo[f][a]) / (2.0 * pn.half[f][a]);
+        const int p = min(max((int)floor(q), 0), pn.panels[f][a] - 1);
+        y = 2.0 * (q - (double)p) - 1.0;
+        return p;
+    };
+    double yu;
+    const int pu_i = panel(0, pu, yu);
+    if (threadIdx.x < 64) {
+        const int i = (int)threadIdx.x;
+        const double d = yu - cospi((double)(2 * i + 1) / (double)(2 * nu));
+        double t = i < nu ? sinpi((double)(2 * i + 1) / (double)(2 * nu)) / d * ((i & 1) ? -1.0 : 1.0) : 0.0;
+        const unsigned long long hit = __ballot(i < nu && d == 0.0);
+        double sum = t;
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if (i < nu) Lu[i] = hit ? (double)((hit >> i) & 1) : t / sum;
+    } else if (threadIdx.x < 128) {
+        const int j = (int)threadIdx.x - 64;
+        if (j < nv) {
+            xs[j] = cospi((double)(2 * j + 1) / (double)(2 * nv));
+            ws[j] = sinpi((double)(2 * j + 1) / (double)(2 * nv)) * ((j & 1) ? -1.0 : 1.0);
+        }
+    }
+    __syncthreads();
+    const double* S = smp + fc.base[f] + (int64_t)pu_i * nu * V;
+    for (int c = threadIdx.x; c < V; c += 256) {
+        double h = 0.0;
+        for (int i = 0; i < nu; ++i) h = fma(Lu[i], S[(int64_t)i * V + c], h);
+        H[c] = h;
+    }
+    __syncthreads();
+    for (int v = threadIdx.x; v < pn.nodes[f][1]; v += 256) {
+        const double pv = node_x(g, va, v + vshift) - cen[va];
+        double yv;
+        const double* h = H + panel(1, pv, yv) * nv;
+        double num = 0.0, den = 0.0, exact = 0.0;
+        bool hit = false;
+        for (int j = 0; j < nv; ++j) {
+            const double d = yv - xs[j];
+            const double t = ws[j] / (d == 0.0 ? 1.0 : d);
+            num = fma(t, h[j], num);
+            den += t;
+            hit = hit || d == 0.0;
+            exact = d == 0.0 ? h[j] : exact;
+        }
+        int c[3];
+        c[w] = side;
+        c[ua] = u + ushift;
+        c[va] = v + vshift;
+        gb[g.idx(c[0], c[1], c[2])] = (hit ? exact : num / den) * dh_centre(kD, pw, pu, pv);
+    }
 }
 
 __global__ void __launch_bounds__(256) k_bc_user(Grid g, const double* full, double* gb)
@@ -1129,6 +1253,17 @@ DhExp dh_exp_consts(double kD)
     return E;
 }
 
+// the numbering of thread patches over faces of U x V points
+static void dh_patches(DhFaces& fc)
+{
+    fc.tile0[0] = 0;
+    for (int f = 0; f < 6; ++f) {
+        fc.pv[f] = (fc.V[f] + DH_PV - 1) / DH_PV;
+        fc.np[f] = (int64_t)((fc.U[f] + DH_PU - 1) / DH_PU) * fc.pv[f];
+        fc.tile0[f + 1] = fc.tile0[f] + (int)((fc.np[f] + 255) / 256);
+    }
+}
+
 DhFaces dh_faces(const Grid& g)
 {
     DhFaces fc{};
@@ -1136,17 +1271,74 @@ DhFaces dh_faces(const Grid& g)
     const int64_t fz = (int64_t)(g.nx - 2) * (g.ny - 2);
     const int U[3] = {g.ny, g.nx - 2, g.nx - 2}, V[3] = {g.nz, g.nz, g.ny - 2};
     const int64_t first[3] = {0, 2 * fx, 2 * fx + 2 * fy}, size[3] = {fx, fy, fz};
-    fc.tile0[0] = 0;
     for (int f = 0; f < 6; ++f) {
         const int w = f >> 1;
         fc.base[f] = first[w] + (f & 1) * size[w];
         fc.U[f] = U[w];
         fc.V[f] = V[w];
-        fc.pv[f] = (V[w] + DH_PV - 1) / DH_PV;
-        fc.np[f] = (int64_t)((U[w] + DH_PU - 1) / DH_PU) * fc.pv[f];
-        fc.tile0[f + 1] = fc.tile0[f] + (int)((fc.np[f] + 255) / 256);
     }
+    dh_patches(fc);
     return fc;
+}
+
+bool dh_interp_plan(const Grid& g, const Atoms& at, const double* lo, const double* hi, double kD, DhInterp* out)
+{
+    DhInterp d{};
+    const DhFaces nodes = dh_faces(g);
+    const double org[3] = {g.ox, g.oy, g.oz}, cen[3] = {at.cx, at.cy, at.cz};
+    const int nn[3] = {g.nx, g.ny, g.nz};
+    int64_t total = 0;
+    for (int f = 0; f < 6; ++f) {
+        const int w = f >> 1, ax[2] = {w == 0 ? 1 : 0, w == 2 ? 1 : 2}, shift[2] = {w == 0 ? 0 : 1, w == 2 ? 1 : 0};
+        const int cnt[2] = {nodes.U[f], nodes.V[f]};
+        // distance of the atoms' centres to the face's plane
+        const double plane = org[w] + g.h * (double)(((f & 1) ? nn[w] - 1 : 0) + g.off[w]);
+        const double D = (f & 1) ? plane - hi[w] : lo[w] - plane;
+        if (!(D > 0.0) || kD * D > 30.0) return false;
+        int S[2];
+        for (int a = 0; a < 2; ++a) {
+            const double x0 = org[ax[a]] + g.h * (double)(shift[a] + g.off[ax[a]]) - cen[ax[a]];
+            const double len = g.h * (double)(cnt[a] - 1);
+            // the fewest panels whose degree stays within kDhMaxDegree; rho^-n = e^(-kD D) 1e-10
+            int P = 1, n = 0;
+            for (;; ++P) {
+                const double q = 2.0 * D * P / std::max(len, g.h);
+                n = (int)std::ceil((23.03 + kD * D) / std::log(q + std::sqrt(q * q + 1.0)));
+                if (n <= kDhMaxDegree) break;
+                if ((int64_t)(P + 1) * kDhMaxDegree > 2 * (int64_t)cnt[a]) return false;
+            }
+            n = std::max(n, 4);
+            d.pn.n[f][a] = n;
+            d.pn.panels[f][a] = P;
+            d.pn.lo[f][a] = x0;
+            d.pn.half[f][a] = 0.5 * std::max(len, g.h) / P;
+            d.pn.nodes[f][a] = cnt[a];
+            S[a] = P * n;
+        }
+        if (S[1] > kDhMaxRow) return false;
+        d.fc.U[f] = S[0];
+        d.fc.V[f] = S[1];
+        d.fc.base[f] = total;
+        total += (int64_t)S[0] * S[1];
+    }
+    dh_patches(d.fc);
+    d.sp = dh_split(g, at.n);
+    // a sample's pairs in FP64 take about 2.5 times a node's in FP32: worth it from 3e8 FP32
+    // pairs saved on (129^3, 3000 atoms, 1.8e8 saved: 150 us against 139 us at every node; 257^3,
+    // 18,000 atoms: 0.73 against 2.27 ms; 385^3, 60,000 atoms: 2.4 against 15.2 ms)
+    const int64_t nbox = d.sp.nbox;
+    if ((double)at.n * ((double)nbox - 2.5 * (double)total) < 3e8) return false;
+    // enough blocks (of 2048 samples each at most) for the device; the partial sums take no more
+    // room than those of all box nodes
+    const int chunks = std::max(1, (at.n + 255) / 256);
+    int64_t r = std::max<int64_t>(1, kDhSampleBlocks / d.fc.tile0[6]);
+    r = std::min(std::min<int64_t>(r, chunks), nbox * d.sp.ranges / total);
+    const int cpr = (int)((chunks + r - 1) / r);
+    d.sp.nbox = total;
+    d.sp.per = 256 * cpr;
+    d.sp.ranges = (chunks + cpr - 1) / cpr;
+    *out = d;
+    return true;
 }
 
 DhSplit dh_split(const Grid& g, int n_atoms)
@@ -1170,7 +1362,7 @@ hipError_t launch_bc_dh(hipStream_t s, const Grid& g, const Atoms& at, double kD
 {
     const DhSplit sp = dh_split(g, at.n);
     const DhFaces fc = dh_faces(g);
-    k_bc_dh<<<(unsigned)(fc.tile0[6] * sp.ranges), 256, 0, s>>>(g, at, dh_exp_consts(kD), sp, fc, part);
+    k_bc_dh<false><<<(unsigned)(fc.tile0[6] * sp.ranges), 256, 0, s>>>(g, at, dh_exp_consts(kD), sp, fc, DhPanels{}, part);
     k_bc_dh_sum<<<(unsigned)nblk(sp.nbox, 256), 256, 0, s>>>(g, sp, part, eps_out, gb);
     return hipGetLastError();
 }
@@ -1182,6 +1374,17 @@ hipError_t launch_bc_dh32(hipStream_t s, const Grid& g, const Atoms& at, double 
     const DhFaces fc = dh_faces(g);
     k_bc_dh32<<<(unsigned)(fc.tile0[6] * sp.ranges), 256, 0, s>>>(g, at, kD, sp, fc, part);
     k_bc_dh_sum<<<(unsigned)nblk(sp.nbox, 256), 256, 0, s>>>(g, sp, part, eps_out, gb);
+    return hipGetLastError();
+}
+
+hipError_t launch_bc_dh_interp(hipStream_t s, const Grid& g, const Atoms& at, double kD, double eps_out,
+                               const DhInterp& d, double* part, double* gb)
+{
+    int rows = 0;
+    for (int f = 0; f < 6; ++f) rows += d.pn.nodes[f][0];
+    k_bc_dh<true><<<(unsigned)(d.fc.tile0[6] * d.sp.ranges), 256, 0, s>>>(g, at, dh_exp_consts(kD), d.sp, d.fc, d.pn, part);
+    k_dh_samples<<<(unsigned)nblk(d.sp.nbox, 256), 256, 0, s>>>(g, at, d.sp, d.fc, d.pn, kD, eps_out, part);
+    k_dh_interp<<<(unsigned)rows, 256, 0, s>>>(g, at, d.fc, d.pn, kD, part, gb);
     return hipGetLastError();
 }
 

@@ -185,6 +185,26 @@ hipError_t launch_bc_dh(hipStream_t s, const Grid& g, const Atoms& at, double kD
                         double* gb);
 hipError_t launch_bc_dh32(hipStream_t s, const Grid& g, const Atoms& at, double kD, double eps_out, double* part,
                           double* gb);
+// The mixed form's box values from samples at the Chebyshev nodes of panels of each face, for atoms
+// far enough from the box that these are fewer than half the box nodes.
+constexpr int kDhMaxDegree = 64;          // most samples per panel and axis (one per lane)
+constexpr int kDhMaxRow = 1024;           // samples per row of a face
+constexpr int64_t kDhSampleBlocks = 4096; // blocks aimed at for the samples
+struct DhPanels {
+    int n[6][2], panels[6][2];       // per face and in-plane axis: samples per panel, panels
+    int nodes[6][2];                 // box nodes of the face along the axis
+    double lo[6][2], half[6][2];     // first node (relative to the atoms' centre), half a panel
+};
+struct DhInterp {
+    DhPanels pn;
+    DhFaces fc;    // the faces as arrays of samples
+    DhSplit sp;    // atom ranges; nbox: samples
+};
+// lo, hi: the atoms' bounding box.  False: the sum at every box node is the better way.
+bool dh_interp_plan(const Grid& g, const Atoms& at, const double* lo, const double* hi, double kD, DhInterp* out);
+// part holds d.sp.ranges * d.sp.nbox doubles
+hipError_t launch_bc_dh_interp(hipStream_t s, const Grid& g, const Atoms& at, double kD, double eps_out,
+                               const DhInterp& d, double* part, double* gb);
 hipError_t launch_bc_user(hipStream_t s, const Grid& g, const double* full, double* gb);
 hipError_t launch_diag_lift(hipStream_t s, const Grid& g, const uint32_t* code, const double* ck64,
                             Coef c, const double* gb, double* rhs, float* dinv, double* diag);
