@@ -172,6 +172,7 @@ struct MGData {
     // layout (the two-level preconditioner of refined grids); made on first use
     void *nat_b = nullptr, *nat_x = nullptr;
     int ls = 0;                 // first level of the part of the V-cycle run in one block
+    bool sub_lds = false;       // that part runs with its levels in LDS
     // the hierarchy's device descriptor, read by every kernel, and the launch tables of the
     // problem solved alone (device; solo_host holds what was copied there)
     void* dev = nullptr;

@@ -462,6 +462,17 @@ __device__ __forceinline__ int64_t colour_node(const Grid& g, int c, int t)
     return g.idx(i, j, k);
 }
 
+// the same node's position, packed as i << 20 | j << 10 | k (32-bit divisions only), or -1
+__device__ __forceinline__ int colour_pos(int nx, int ny, int nz, int c, int t)
+{
+    const unsigned M = (unsigned)(nz - 1) >> 1, rows = (unsigned)((nx - 2) * (ny - 2));
+    if (M == 0 || (unsigned)t >= rows * M) return -1;
+    const unsigned row = (unsigned)t / M, m = (unsigned)t - row * M;
+    const unsigned i = 1 + row / (unsigned)(ny - 2), j = 1 + row % (unsigned)(ny - 2);
+    const unsigned k = 1 + ((i + j + 1 + (unsigned)c) & 1) + 2 * m;
+    return k > (unsigned)(nz - 2) ? -1 : (int)((i << 20) | (j << 10) | k);
+}
+
 __device__ __forceinline__ int64_t interior_node(const Grid& g, int t, bool& red)
 {
     const int nzi = g.nz - 2, nyi = g.ny - 2;
@@ -766,6 +777,286 @@ __global__ void __launch_bounds__(kSubThreads) kb_subcycle(Bt<T> B, GateSpec gs)
             blk_sweep(L, 0);
         }
     }
+}
+
+// The same part of the V-cycle with its levels held in LDS and registers.  In kb_subcycle every
+// phase loads its coefficients and vectors from global memory, 1.2 us a phase and mostly latency;
+// here they are loaded once, all levels together, and a phase is a few LDS reads: the coefficients
+// and right-hand side of the first level's nodes in the registers of the thread that owns them
+// (kSubOwn of each colour), its iterate and red residual in LDS, and of the deeper levels (under
+// 1024 unknowns in all their slots) everything in LDS.  Same steps and order, same bits.
+// In FP32 21 us in place of 40 where the first level has 17^3 nodes (grids of 65^3 and 129^3), 27
+// in place of 48 for 21^3 (161^3); about 6 us of it is the loads of the first level's coefficients,
+// which one compute unit's cache path serves.  Levels too large for this keep kb_subcycle.
+template <typename T>
+constexpr int kSubOwn = sizeof(T) == 4 ? 4 : 2;   // nodes of a colour per thread (registers)
+constexpr size_t kSubLdsBytes = 144 * 1024;
+constexpr int kSubMaxDeep = PB_MG_MAX_LEVELS;
+
+// LDS use in elements of T: first level x and r, deeper levels seven arrays; then the packed node
+// positions of the deeper levels' colour slots (uint32)
+inline size_t sub_lds_bytes(size_t elem, const Grid* g, int ls, int nlev)
+{
+    auto nodes = [](const Grid& q) { return (size_t)q.nx * q.ny * q.nz; };
+    size_t e = 2 * nodes(g[ls]), slots = 0;
+    for (int l = ls + 1; l < nlev; ++l) {
+        e += 7 * nodes(g[l]);
+        slots += 2 * (size_t)colour_threads(g[l]);
+    }
+    return e * elem + 4 * slots;
+}
+
+struct SubLev {   // a deeper level in LDS: element offset of its arrays, first packed position
+    int nx, ny, nz, n, slots, base, tab;
+};
+
+template <typename T>
+__global__ void __launch_bounds__(kSubThreads) kb_sub_lds(Bt<T> B, GateSpec gs)
+{
+    constexpr int W = kSubOwn<T>;
+    __shared__ __attribute__((aligned(16))) char mem[kSubLdsBytes];
+    __shared__ SubLev lev[kSubMaxDeep];
+    int local;
+    const GMEM MGDev<T>& D = *B.d[bt_find(B.off, B.P, local)];
+    if (gated_out(gs, D.st)) return;
+    const int l0 = D.ls, nl = D.nlev, tid = (int)threadIdx.x;
+    const Lev<T> L = D.lv[l0];
+    const Grid& g = L.g;
+    const int n0 = g.nx * g.ny * g.nz, sy = g.nz, sx = g.ny * g.nz;
+    T* X = (T*)mem;
+    T* R = X + n0;
+    const int nd = nl - 1 - l0, nu = D.nu, cs = D.cs;
+    // the deeper levels' dimensions (one level per lane), then their places in LDS
+    if (tid < nd) {
+        SubLev& v = lev[tid];
+        v.nx = D.lv[l0 + 1 + tid].g.nx;
+        v.ny = D.lv[l0 + 1 + tid].g.ny;
+        v.nz = D.lv[l0 + 1 + tid].g.nz;
+        v.n = v.nx * v.ny * v.nz;
+        v.slots = (v.nx - 2) * (v.ny - 2) * ((v.nz - 1) >> 1);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int e = 2 * n0, s = 0;
+        for (int l = 0; l < nd; ++l) {
+            lev[l].base = e;
+            lev[l].tab = s;
+            e += 7 * lev[l].n;
+            s += 2 * lev[l].slots;
+        }
+        lev[nd].base = e;   // end of the elements: the packed positions follow
+        lev[nd].n = (e - 2 * n0) / 7;   // nodes of all deeper levels
+    }
+    // the first level's own nodes: position, six edge weights, 1/D, right-hand side, D (red)
+    T k[2][W][6], di[2][W], b[2][W], dg[W];
+    int pos[2][W];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            // a slot without a node loads those of node (1, 1, 1) and never uses them: with no
+            // branch, the loads of all slots are in flight together
+            const int p = colour_pos(g.nx, g.ny, g.nz, c, tid + q * kSubThreads);
+            pos[c][q] = p;
+            const int u = p < 0 ? (1 << 20) | (1 << 10) | 1 : p, gx = g.ny * g.S, gy = g.S;
+            const int e = ((u >> 20) * g.ny + ((u >> 10) & 1023)) * g.S + (u & 1023) + Z0;
+            k[c][q][0] = L.kx[e - gx];
+            k[c][q][1] = L.kx[e];
+            k[c][q][2] = L.ky[e - gy];
+            k[c][q][3] = L.ky[e];
+            k[c][q][4] = L.kz[e - 1];
+            k[c][q][5] = L.kz[e];
+            di[c][q] = L.dinv[e];
+            b[c][q] = L.b[e];
+            if (c == 0) dg[q] = L.diag[e];
+        }
+    __syncthreads();
+    int* tab = (int*)(mem + sizeof(T) * (size_t)lev[nd].base);
+    for (int t = tid; t < n0; t += kSubThreads) X[t] = (T)0;
+    // the deeper levels' arrays, all levels as one list of nodes
+    for (int t0 = tid; t0 < lev[nd].n; t0 += 2 * kSubThreads) {
+        T val[2][5];
+        int dst[2], n[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            int t = t0 + u * kSubThreads, l = 0;
+            t = t < lev[nd].n ? t : t0;
+            while (t >= lev[l].n) t -= lev[l++].n;
+            const SubLev v = lev[l];
+            const GMEM Lev<T>& C = D.lv[l0 + 1 + l];
+            const unsigned row = (unsigned)t / (unsigned)v.nz;
+            const int e = (int)row * C.g.S + (t - (int)row * v.nz) + Z0;
+            val[u][0] = C.kx[e];
+            val[u][1] = C.ky[e];
+            val[u][2] = C.kz[e];
+            val[u][3] = C.dinv[e];
+            val[u][4] = C.diag[e];
+            dst[u] = v.base + t;
+            n[u] = v.n;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            T* a = X + dst[u];   // x, b, kx, ky, kz, 1/D, D
+            a[0] = (T)0;
+            for (int f = 0; f < 5; ++f) a[(2 + f) * n[u]] = val[u][f];
+        }
+    }
+    for (int l = 0; l < nd; ++l) {
+        const SubLev v = lev[l];
+        for (int t = tid; t < 2 * v.slots; t += kSubThreads) {
+            const int c = t >= v.slots ? 1 : 0;
+            tab[v.tab + t] = colour_pos(v.nx, v.ny, v.nz, c, t - c * v.slots);
+        }
+    }
+    __syncthreads();
+    auto at0 = [&](int p) { return (p >> 20) * sx + ((p >> 10) & 1023) * sy + (p & 1023); };
+    // one half-sweep of the first level (fresh: from a zero iterate, x = b / D)
+    auto own_sweep = [&](auto colour, bool fresh) {
+        constexpr int c = decltype(colour)::value;
+#pragma unroll
+        for (int q = 0; q < W; ++q)
+            if (pos[c][q] >= 0) {
+                const int o = at0(pos[c][q]);
+                if (fresh) {
+                    X[o] = b[c][q] * di[c][q];
+                } else {
+                    const T* K = k[c][q];
+                    const T s = ((K[0] * X[o - sx] + K[1] * X[o + sx]) + (K[2] * X[o - sy] + K[3] * X[o + sy])) +
+                                (K[4] * X[o - 1] + K[5] * X[o + 1]);
+                    X[o] = (b[c][q] + s) * di[c][q];
+                }
+            }
+        __syncthreads();
+    };
+    // one half-sweep of a deeper level (fresh as above), or with resid the residual at its red nodes
+    auto deep_sum = [&](const SubLev& v, const T* a, int o) {
+        const int dy = v.nz, dx = v.ny * v.nz;
+        const T *kx = a + 2 * v.n, *ky = a + 3 * v.n, *kz = a + 4 * v.n;
+        return ((kx[o - dx] * a[o - dx] + kx[o] * a[o + dx]) + (ky[o - dy] * a[o - dy] + ky[o] * a[o + dy])) +
+               (kz[o - 1] * a[o - 1] + kz[o] * a[o + 1]);
+    };
+    auto deep_sweep = [&](const SubLev& v, int c, bool fresh) {
+        T* a = X + v.base;
+        if (tid < v.slots) {
+            const int p = tab[v.tab + c * v.slots + tid];
+            if (p >= 0) {
+                const int o = ((p >> 20) * v.ny + ((p >> 10) & 1023)) * v.nz + (p & 1023);
+                const T bb = a[v.n + o], d = a[5 * v.n + o];
+                a[o] = fresh ? bb * d : (bb + deep_sum(v, a, o)) * d;
+            }
+        }
+        __syncthreads();
+    };
+    // restriction of the red residual r of a level (ny, nz its nodes per axis) to level v
+    auto restrict_to = [&](const SubLev& v, const T* r, int fy, int fz) {
+        T* bc = X + v.base + v.n;
+        const int cz = v.nz - 2, cy = v.ny - 2, n = (v.nx - 2) * cy * cz;
+        if (tid < n) {
+            const int row = (int)((unsigned)tid / (unsigned)cz), K = 1 + tid - row * cz;
+            const int I = 1 + (int)((unsigned)row / (unsigned)cy), J = 1 + row - (I - 1) * cy;
+            const int dx = fy * fz, dy = fz, f = (2 * I * fy + 2 * J) * fz + 2 * K;
+            const T xy = (r[f - dx - dy] + r[f - dx + dy]) + (r[f + dx - dy] + r[f + dx + dy]);
+            const T xz = (r[f - dx - 1] + r[f - dx + 1]) + (r[f + dx - 1] + r[f + dx + 1]);
+            const T yz = (r[f - dy - 1] + r[f - dy + 1]) + (r[f + dy - 1] + r[f + dy + 1]);
+            bc[(I * v.ny + J) * v.nz + K] = r[f] + (T)0.25 * ((xy + xz) + yz);
+        }
+        __syncthreads();
+    };
+    // P e at fine node p (packed) from level v
+    auto prolong = [&](const SubLev& v, int p) {
+        const T* e = X + v.base;
+        const int i = p >> 20, j = (p >> 10) & 1023, kk = p & 1023;
+        const int i0 = (i >> 1) * v.ny, i1 = ((i + 1) >> 1) * v.ny, j0 = j >> 1, j1 = (j + 1) >> 1, k0 = kk >> 1,
+                  k1 = (kk + 1) >> 1;
+        auto E = [&](int r, int z) { return e[r * v.nz + z]; };
+        const T s = ((E(i0 + j0, k0) + E(i0 + j0, k1)) + (E(i0 + j1, k0) + E(i0 + j1, k1))) +
+                    ((E(i1 + j0, k0) + E(i1 + j0, k1)) + (E(i1 + j1, k0) + E(i1 + j1, k1)));
+        return (T)0.125 * s;
+    };
+    using Red = std::integral_constant<int, 0>;
+    using Black = std::integral_constant<int, 1>;
+    own_sweep(Red{}, true);
+    if (nl - 1 == l0) {
+        for (int v = 0; v < cs; ++v) {
+            own_sweep(Black{}, false);
+            own_sweep(Red{}, false);
+        }
+    } else {
+        // down
+        own_sweep(Black{}, false);
+        for (int v = 1; v < nu; ++v) {
+            own_sweep(Red{}, false);
+            own_sweep(Black{}, false);
+        }
+#pragma unroll
+        for (int q = 0; q < W; ++q)
+            if (pos[0][q] >= 0) {
+                const int o = at0(pos[0][q]);
+                const T* K = k[0][q];
+                const T s = ((K[0] * X[o - sx] + K[1] * X[o + sx]) + (K[2] * X[o - sy] + K[3] * X[o + sy])) +
+                            (K[4] * X[o - 1] + K[5] * X[o + 1]);
+                R[o] = b[0][q] - (dg[q] * X[o] - s);
+            }
+        __syncthreads();
+        restrict_to(lev[0], R, g.ny, g.nz);
+        for (int l = l0 + 1; l + 1 < nl; ++l) {
+            const SubLev v = lev[l - l0 - 1];
+            deep_sweep(v, 0, true);
+            deep_sweep(v, 1, false);
+            for (int u = 1; u < nu; ++u) {
+                deep_sweep(v, 0, false);
+                deep_sweep(v, 1, false);
+            }
+            const T* a = X + v.base;
+            if (tid < v.slots) {
+                const int p = tab[v.tab + tid];
+                if (p >= 0) {
+                    const int o = ((p >> 20) * v.ny + ((p >> 10) & 1023)) * v.nz + (p & 1023);
+                    R[o] = a[v.n + o] - (a[6 * v.n + o] * a[o] - deep_sum(v, a, o));
+                }
+            }
+            __syncthreads();
+            restrict_to(lev[l - l0], R, v.ny, v.nz);
+        }
+        // coarsest: red from zero, then (black, red) x cs
+        {
+            const SubLev v = lev[nl - l0 - 2];
+            deep_sweep(v, 0, true);
+            for (int u = 0; u < cs; ++u) {
+                deep_sweep(v, 1, false);
+                deep_sweep(v, 0, false);
+            }
+        }
+        // up
+        for (int l = nl - 2; l > l0; --l) {
+            const SubLev v = lev[l - l0 - 1], vc = lev[l - l0];
+            T* a = X + v.base;
+            if (tid < v.slots) {
+                const int p = tab[v.tab + tid];
+                if (p >= 0) a[((p >> 20) * v.ny + ((p >> 10) & 1023)) * v.nz + (p & 1023)] += prolong(vc, p);
+            }
+            __syncthreads();
+            for (int u = 0; u < nu; ++u) {
+                deep_sweep(v, 1, false);
+                deep_sweep(v, 0, false);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < W; ++q)
+            if (pos[0][q] >= 0) X[at0(pos[0][q])] += prolong(lev[0], pos[0][q]);
+        __syncthreads();
+        for (int u = 0; u < nu; ++u) {
+            own_sweep(Black{}, false);
+            own_sweep(Red{}, false);
+        }
+    }
+    // the first level's iterate, which the level above prolongs from
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int q = 0; q < W; ++q)
+            if (pos[c][q] >= 0)
+                L.x[g.idx(pos[c][q] >> 20, (pos[c][q] >> 10) & 1023, pos[c][q] & 1023)] = X[at0(pos[c][q])];
 }
 
 // ---- level 0 (red-black layout) ------------------------------------------------------------
@@ -1494,7 +1785,7 @@ Op0<T> op0(const pb_problem* pb)
 // ---- launch plans --------------------------------------------------------------------------
 // A plan lists, for a set of problems, how many blocks each has in every kind of pass: the
 // level-0 passes (and the streaming CG passes, which use as many blocks), the one-block scalar
-// steps, the one-block small levels, a one-block coarsest level, a large coarsest level
+// steps, the one-block small levels (in global memory, or in LDS), a one-block coarsest level, a large coarsest level
 // (all nodes / one colour), and per coarse level l the pre/post-smoothing passes (all nodes /
 // one colour) and the restriction onto it.  The block offsets of every pass kind go to the
 // device in one table.
@@ -1502,6 +1793,7 @@ enum PassKind {
     K_RB0 = 0,
     K_ONE,
     K_SUB,
+    K_SUBL,
     K_COARSE1,
     K_CALL,
     K_CCOL,
@@ -1526,7 +1818,7 @@ void pass_counts(const MGData* G, int* cnt)
     }
     for (int l = 1; l <= top; ++l) cnt[K_RES + l] = lev_blocks(G->g[l], false);
     if (G->ls < L) {
-        cnt[K_SUB] = 1;
+        cnt[G->sub_lds ? K_SUBL : K_SUB] = 1;
     } else if (interior_count(G->g[L - 1]) <= kOneBlockCoarse) {
         cnt[K_COARSE1] = 1;
     } else {
@@ -1624,6 +1916,7 @@ void run_vcycle(hipStream_t s, const Plan& pl, GateSpec gs, hipEvent_t* ev = nul
     }
     // the small levels in one block, or the coarsest level
     PLAUNCH(K_SUB, kSubThreads, kb_subcycle<T>, gs);
+    PLAUNCH(K_SUBL, kSubThreads, kb_sub_lds<T>, gs);
     PLAUNCH(K_COARSE1, 256, kb_coarse<T>, gs);
     if (pl.total[K_CALL] > 0) {
         // red, black in one pass, then red, then (black, red) x (cs - 1)
@@ -1771,6 +2064,10 @@ int setup_levels(pb_problem* pb, MGData* G, hipStream_t s)
     // the first level from which every level has at most kSubcycleNodes unknowns (not 0)
     G->ls = G->nlev;
     while (G->ls - 1 >= 1 && interior_count(G->g[G->ls - 1]) <= kSubcycleNodes) --G->ls;
+    // those levels in LDS and registers where they fit
+    G->sub_lds = G->ls < G->nlev && G->g[G->ls].nx < 2048 && G->g[G->ls].ny < 1024 && G->g[G->ls].nz < 1024 &&
+                 colour_threads(G->g[G->ls]) <= (int64_t)kSubOwn<T> * kSubThreads &&
+                 sub_lds_bytes(sizeof(T), G->g, G->ls, G->nlev) <= kSubLdsBytes;
     // FP64 coefficients of every coarse level, then the element-type copies
     const double *pkx = nullptr, *pky = nullptr, *pkz = nullptr, *pm = nullptr;
     for (int l = 1; l < G->nlev; ++l) {
