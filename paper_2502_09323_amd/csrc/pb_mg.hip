@@ -105,6 +105,7 @@ struct RB {
     int Sh;        // positions per colour segment (a multiple of 32: 128-byte aligned segments)
     int64_t N;     // elements per vector: nx * ny * 2 * Sh
     int lw;        // a wave of a level-0 pass covers 2^lw positions of 64 >> lw rows
+    int pl;        // x-planes per thread of a level-0 pass
     __host__ __device__ int64_t at(int i, int j, int c, int m) const
     {
         return (((int64_t)i * ny + j) * 2 + c) * Sh + m;
@@ -206,16 +207,33 @@ __device__ __forceinline__ bool gated_out(const GateSpec& g, const GMEM CGState*
     return st->status != 0 || st->ru != g.mode;
 }
 
-// The block shape of the per-node passes: 64 lanes along z by 4 rows along y, each thread
-// taking kPlanes x-planes, so that no thread divides to find its node and a launch has few
-// enough blocks that one which finds the iteration stopped costs little.
+// The block shape of the coarse levels' per-node passes: 64 lanes along z by 4 rows along y, each
+// thread taking kPlanes x-planes, so that no thread divides to find its node and a launch has few
+// enough blocks that one which finds the iteration stopped costs little; one plane where that would
+// be fewer than kBlocksLev blocks, which leaves compute units idle through a thread's planes (one
+// solve: 65^3 2.87 -> 2.60 ms, 129^3 5.16 -> 4.68, two at 161^3 13.9 -> 13.35; from 256 or 1024
+// blocks on: 129^3 4.85 and 4.67, 385^3 the same within 0.3 %).
 constexpr int kPlanes = 4;
-// level 0 (red-black layout): more x-planes per thread, so that fewer neighbour planes are
-// read again at the edges of a block's slab
-#ifndef PB_PLANES_RB
-#define PB_PLANES_RB 8
-#endif
-constexpr int kPlanesRB = PB_PLANES_RB;
+constexpr int kBlocksLev = 512;
+
+// Level 0 (red-black layout): 8 x-planes per thread, so that few neighbour planes are read again
+// at the edges of a block's slab; kFewPlanes where the launch would have fewer than kBlocksRB
+// blocks, so that a small grid's compute units do not go through eight planes one after the other
+// while most of the device idles.  65^3 (64 blocks at 8 planes): half-sweep 7.4 -> 4.2 us, operator
+// pass 12.4 -> 6.5; 129^3 (512): 13.3 -> 10.2 and 19.4 -> 15.8; 161^3 (1000): the same either way;
+// one plane instead of two: 129^3 a tenth slower per solve, 65^3 the same.
+constexpr int kManyPlanes = 8, kFewPlanes = 2;
+constexpr int64_t kBlocksRB = 768;
+
+// f with the planes per thread as a constant, for unrolled loops over them
+template <typename F>
+__device__ __forceinline__ void by_planes(int pl, F f)
+{
+    if (pl == kManyPlanes)
+        f(std::integral_constant<int, kManyPlanes>{});
+    else
+        f(std::integral_constant<int, kFewPlanes>{});
+}
 
 struct VB {   // a block of a problem's own 3-D launch
     int x, y, z;
@@ -238,7 +256,16 @@ __host__ __device__ inline int rb_rows(const RB& r) { return 4 * (64 >> r.lw); }
 __host__ __device__ inline int rb_gy(const RB& r) { return (r.ny - 2 + rb_rows(r) - 1) / rb_rows(r); }
 __host__ __device__ inline int rows_gy(int ny) { return (ny - 2 + 3) / 4; }
 
-inline int rb_blocks(const RB& r) { return rb_gx(r) * rb_gy(r) * ((r.nx - 2 + kPlanesRB - 1) / kPlanesRB); }
+inline int rb_blocks(const RB& r) { return rb_gx(r) * rb_gy(r) * ((r.nx - 2 + r.pl - 1) / r.pl); }
+
+// the tiling of a problem's level-0 passes
+inline RB rb_tiled(const Grid& g)
+{
+    RB r = rb_of(g);
+    r.pl = kManyPlanes;
+    if (rb_blocks(r) < kBlocksRB) r.pl = kFewPlanes;
+    return r;
+}
 
 // block `local` of a level-0 pass of nb blocks takes tile item(local): blocks are dealt to the
 // 8 XCDs round-robin (a problem's blocks start at a multiple of 8), and this bijection gives
@@ -259,9 +286,26 @@ __host__ __device__ inline int lev_gx(const Grid& g, bool colour)
     return nzl > 0 ? (nzl + 63) / 64 : 1;
 }
 
+// planes per thread of a coarse level's passes
+__host__ __device__ inline int lev_planes(const Grid& g)
+{
+    return lev_gx(g, false) * rows_gy(g.ny) * ((g.nx - 2 + kPlanes - 1) / kPlanes) < kBlocksLev ? 1 : kPlanes;
+}
+
 inline int lev_blocks(const Grid& g, bool colour)
 {
-    return lev_gx(g, colour) * rows_gy(g.ny) * ((g.nx - 2 + kPlanes - 1) / kPlanes);
+    const int pl = lev_planes(g);
+    return lev_gx(g, colour) * rows_gy(g.ny) * ((g.nx - 2 + pl - 1) / pl);
+}
+
+// f with the planes per thread as a constant
+template <typename F>
+__device__ __forceinline__ void by_lev_planes(const Grid& g, F f)
+{
+    if (lev_planes(g) == 1)
+        f(std::integral_constant<int, 1>{});
+    else
+        f(std::integral_constant<int, kPlanes>{});
 }
 
 __device__ __forceinline__ VB vb_lev(const Grid& g, bool colour, int local)
@@ -275,7 +319,7 @@ __device__ __forceinline__ bool rb_slot(const VB& b, const RB& r, int p, int& i,
     const int lane = (int)(threadIdx.x & 63), w = 1 << r.lw;
     m = b.x * w + (lane & (w - 1));
     j = 1 + b.y * rb_rows(r) + (int)(threadIdx.x >> 6) * (64 >> r.lw) + (lane >> r.lw);
-    i = 1 + b.z * kPlanesRB + p;
+    i = 1 + b.z * r.pl + p;
     return i <= r.nx - 2 && j <= r.ny - 2;
 }
 
@@ -298,12 +342,12 @@ struct RBFrame {
 __device__ __forceinline__ RBFrame rb_frame(const RB& r, const VB& vb)
 {
     RBFrame f;
-    f.i0 = 1 + vb.z * kPlanesRB;
+    f.i0 = 1 + vb.z * r.pl;
     f.org = (int64_t)(f.i0 - 1) * r.ny * 2 * r.Sh;
     return f;
 }
 
-// offset of (i, j, c, m) in a frame (planes i0 - 1 ... i0 + kPlanesRB)
+// offset of (i, j, c, m) in a frame (planes i0 - 1 ... i0 + pl)
 __device__ __forceinline__ uint32_t rb_rel(const RB& r, const RBFrame& f, int i, int j, int c, int m)
 {
     return ((uint32_t)((i - f.i0 + 1) * r.ny + j) * 2u + (uint32_t)c) * (uint32_t)r.Sh + (uint32_t)m;
@@ -377,20 +421,20 @@ __device__ __forceinline__ stencil::NodeK<T> rb_k(const OpRB<T>& op, const GMEM 
     return k;
 }
 
-// A level-0 stencil pass first loads the codes of all its thread's nodes (kPlanesRB x NC,
+// A level-0 stencil pass first loads the codes of all its thread's nodes (P planes x NC,
 // NC colours per plane; C_RB_UNCUT where a slot has no node), then takes one of two
 // branch-free bodies for the whole wave: the uncut one where every node of the wave carries
 // C_RB_UNCUT, else the table one.  With no branch on loaded data inside the body, the loads of
 // all planes can be in flight together.  The one-colour passes load these codes
 // non-temporal (385^3: 3-5 % less time); the operator pass, which reads neighbours' codes
 // too, keeps them cached.
-template <int NC>
+template <int P, int NC>
 __device__ __forceinline__ bool rb_codes(const VB& vb, const RB& R, const RBFrame& F, const GMEM uint32_t* code,
                                          int c0, uint32_t (*cc)[NC])
 {
     bool uncut = true;
 #pragma unroll
-    for (int p = 0; p < kPlanesRB; ++p) {
+    for (int p = 0; p < P; ++p) {
         int i, j, m;
         const bool ok = rb_slot(vb, R, p, i, j, m);
 #pragma unroll
@@ -401,7 +445,7 @@ __device__ __forceinline__ bool rb_codes(const VB& vb, const RB& R, const RBFram
         }
     }
 #pragma unroll
-    for (int p = 0; p < kPlanesRB; ++p)
+    for (int p = 0; p < P; ++p)
 #pragma unroll
         for (int q = 0; q < NC; ++q) uncut = uncut && (cc[p][q] & C_RB_UNCUT) != 0;
     return __all(uncut) != 0;
@@ -427,23 +471,26 @@ __device__ __forceinline__ T nsum(const Lev<T>& L, int64_t e, F v, T* D = nullpt
            (L.kz[e - 1] * v(e - 1) + L.kz[e] * v(e + 1));
 }
 
-// interior node of this thread in plane r of its block (all nodes), or -1; red tells its colour
-__device__ __forceinline__ int64_t this_node(const VB& b, const Grid& g, int r, bool& red)
+// interior node of this thread in plane r of the pl of its block (all nodes), or -1; red tells its
+// colour
+__device__ __forceinline__ int64_t this_node(const VB& b, const Grid& g, int pl, int r, bool& red)
 {
     const int k = 1 + b.x * 64 + (int)(threadIdx.x & 63);
     const int j = 1 + b.y * 4 + (int)(threadIdx.x >> 6);
-    const int i = 1 + b.z * kPlanes + r;
+    const int i = 1 + b.z * pl + r;
     if (k > g.nz - 2 || j > g.ny - 2 || i > g.nx - 2) return -1;
     red = ((i + j + k) & 1) == 0;
     return g.idx(i, j, k);
 }
 
-// interior node of colour c (0 red, 1 black) of this thread in plane r, or -1; with its indices
-__device__ __forceinline__ int64_t this_colour_node(const VB& b, const Grid& g, int c, int r, int& i, int& j, int& k)
+// interior node of colour c (0 red, 1 black) of this thread in plane r of the pl of its block, or
+// -1; with its indices
+__device__ __forceinline__ int64_t this_colour_node(const VB& b, const Grid& g, int c, int pl, int r, int& i, int& j,
+                                                    int& k)
 {
     const int m = b.x * 64 + (int)(threadIdx.x & 63);
     j = 1 + b.y * 4 + (int)(threadIdx.x >> 6);
-    i = 1 + b.z * kPlanes + r;
+    i = 1 + b.z * pl + r;
     k = 1 + ((i + j + 1 + c) & 1) + 2 * m;
     if (k > g.nz - 2 || j > g.ny - 2 || i > g.nx - 2) return -1;
     return g.idx(i, j, k);
@@ -522,10 +569,12 @@ __global__ void __launch_bounds__(256) kb_down1(Bt<T> B, int l, GateSpec gs)
     const VB vb = vb_lev(L.g, false, local);
     const GMEM T* __restrict__ b = L.b;
     const GMEM T* __restrict__ dinv = L.dinv;
+    by_lev_planes(L.g, [&](auto PL) {
+        constexpr int P = decltype(PL)::value;
 #pragma unroll
-    for (int r = 0; r < kPlanes; ++r) {
+    for (int r = 0; r < P; ++r) {
         bool red;
-        const int64_t e = this_node(vb, L.g, r, red);
+        const int64_t e = this_node(vb, L.g, P, r, red);
         if (e < 0) continue;
         if (red) {
             L.x[e] = b[e] * dinv[e];
@@ -534,6 +583,7 @@ __global__ void __launch_bounds__(256) kb_down1(Bt<T> B, int l, GateSpec gs)
             L.x[e] = (b[e] + s) * dinv[e];
         }
     }
+    });
 }
 
 // Gauss-Seidel on the nodes of colour c of coarse level l
@@ -546,14 +596,17 @@ __global__ void __launch_bounds__(256) kb_sweep(Bt<T> B, int l, int c, GateSpec 
     const Lev<T> L = D.lv[lev_index(D, l)];
     const VB vb = vb_lev(L.g, true, local);
     const GMEM T* __restrict__ x = L.x;
+    by_lev_planes(L.g, [&](auto PL) {
+        constexpr int P = decltype(PL)::value;
 #pragma unroll
-    for (int r = 0; r < kPlanes; ++r) {
+    for (int r = 0; r < P; ++r) {
         int i, j, k;
-        const int64_t e = this_colour_node(vb, L.g, c, r, i, j, k);
+        const int64_t e = this_colour_node(vb, L.g, c, P, r, i, j, k);
         if (e < 0) continue;
         const T s = nsum<T>(L, e, [&](int64_t n) { return x[n]; });
         L.x[e] = (L.b[e] + s) * L.dinv[e];
     }
+    });
 }
 
 // residual b - A x at the red nodes of coarse level l (after a black half-sweep the black
@@ -568,15 +621,18 @@ __global__ void __launch_bounds__(256) kb_resid(Bt<T> B, int l, GateSpec gs)
     GMEM T* __restrict__ r = D.r[l];
     const VB vb = vb_lev(L.g, true, local);
     const GMEM T* __restrict__ x = L.x;
+    by_lev_planes(L.g, [&](auto PL) {
+        constexpr int P = decltype(PL)::value;
 #pragma unroll
-    for (int p = 0; p < kPlanes; ++p) {
+    for (int p = 0; p < P; ++p) {
         int i, j, k;
-        const int64_t e = this_colour_node(vb, L.g, 0, p, i, j, k);
+        const int64_t e = this_colour_node(vb, L.g, 0, P, p, i, j, k);
         if (e < 0) continue;
         T Dg;
         const T s = nsum<T>(L, e, [&](int64_t n) { return x[n]; }, &Dg);
         r[e] = L.b[e] - (Dg * x[e] - s);
     }
+    });
 }
 
 // coarse right-hand side P^T r on level l from the red residual of level l - 1: fine node 2I
@@ -591,14 +647,16 @@ __global__ void __launch_bounds__(256) kb_restrict(Bt<T> B, int l, GateSpec gs)
     const Grid gc = D.lv[l].g;
     GMEM T* __restrict__ bc = const_cast<GMEM T*>(D.lv[l].b);
     const VB vb = vb_lev(gc, false, local);
+    by_lev_planes(gc, [&](auto PL) {
+        constexpr int P = decltype(PL)::value;
 #pragma unroll
-    for (int p = 0; p < kPlanes; ++p) {
+    for (int p = 0; p < P; ++p) {
         bool red;
-        const int64_t ec = this_node(vb, gc, p, red);
+        const int64_t ec = this_node(vb, gc, P, p, red);
         if (ec < 0) continue;
         const int K = 1 + vb.x * 64 + (int)(threadIdx.x & 63);
         const int J = 1 + vb.y * 4 + (int)(threadIdx.x >> 6);
-        const int I = 1 + vb.z * kPlanes + p;
+        const int I = 1 + vb.z * P + p;
         const int i = 2 * I, j = 2 * J, k = 2 * K;
         if (l == 1) {
             const GMEM T* __restrict__ r = D.r0;
@@ -618,6 +676,7 @@ __global__ void __launch_bounds__(256) kb_restrict(Bt<T> B, int l, GateSpec gs)
             bc[ec] = r[f] + (T)0.25 * ((xy + xz) + yz);
         }
     }
+    });
 }
 
 // x += P e at the red nodes of coarse level l from level l + 1: post-smoothing starts with a
@@ -632,13 +691,16 @@ __global__ void __launch_bounds__(256) kb_prolong(Bt<T> B, int l, GateSpec gs)
     const Grid gc = D.lv[l + 1].g;
     const GMEM T* __restrict__ ec = D.lv[l + 1].x;
     const VB vb = vb_lev(L.g, true, local);
+    by_lev_planes(L.g, [&](auto PL) {
+        constexpr int P = decltype(PL)::value;
 #pragma unroll
-    for (int p = 0; p < kPlanes; ++p) {
+    for (int p = 0; p < P; ++p) {
         int i, j, k;
-        const int64_t e = this_colour_node(vb, L.g, 0, p, i, j, k);
+        const int64_t e = this_colour_node(vb, L.g, 0, P, p, i, j, k);
         if (e < 0) continue;
         L.x[e] += prolong_at(gc, ec, i, j, k);
     }
+    });
 }
 
 // the coarsest level in one block: red from zero, then (black, red) x cs
@@ -1089,11 +1151,13 @@ __global__ void __launch_bounds__(256) kb_rb_down1(Bt<T> B, GateSpec gs)
     const GMEM T* b = D.cr + F.org;
     const GMEM T* dinv = D.dinv0 + F.org;
     GMEM T* x = D.cz + F.org;
-    uint32_t cc[kPlanesRB][1];
-    const bool uncut = rb_codes<1>(vb, R, F, code, 1, cc);
+    by_planes(R.pl, [&](auto PL) {
+    constexpr int P = decltype(PL)::value;
+    uint32_t cc[P][1];
+    const bool uncut = rb_codes<P, 1>(vb, R, F, code, 1, cc);
     auto body = [&](auto U) {
 #pragma unroll
-        for (int p = 0; p < kPlanesRB; ++p) {
+        for (int p = 0; p < P; ++p) {
             int i, j, m;
             if (!rb_slot(vb, R, p, i, j, m)) continue;
             if (rb_node(R, i, j, 0, m) >= 0) {
@@ -1113,6 +1177,7 @@ __global__ void __launch_bounds__(256) kb_rb_down1(Bt<T> B, GateSpec gs)
         body(std::true_type{});
     else
         body(std::false_type{});
+    });
 }
 
 // Gauss-Seidel on the level-0 nodes of colour c; with dot (the last red half-sweep of a
@@ -1133,12 +1198,14 @@ __global__ void __launch_bounds__(256) kb_rb_sweep(Bt<T> B, int c, GateSpec gs)
     const GMEM T* b = D.cr + F.org;
     const GMEM T* dinv = D.dinv0 + F.org;
     GMEM T* x = D.cz + F.org;
-    uint32_t cc[kPlanesRB][1];
-    const bool uncut = rb_codes<1>(vb, R, F, code, c, cc);
     double v[1] = {0.0};
+    by_planes(R.pl, [&](auto PL) {
+    constexpr int P = decltype(PL)::value;
+    uint32_t cc[P][1];
+    const bool uncut = rb_codes<P, 1>(vb, R, F, code, c, cc);
     auto body = [&](auto U) {
 #pragma unroll
-        for (int p = 0; p < kPlanesRB; ++p) {
+        for (int p = 0; p < P; ++p) {
             int i, j, m;
             if (!rb_slot(vb, R, p, i, j, m)) continue;
             const int k = rb_node(R, i, j, c, m);
@@ -1163,6 +1230,7 @@ __global__ void __launch_bounds__(256) kb_rb_sweep(Bt<T> B, int c, GateSpec gs)
         body(std::true_type{});
     else
         body(std::false_type{});
+    });
     if constexpr (Dot) {
         bsum(v, 1, sh);
         if (threadIdx.x == 0) D.prz[local] = v[0];
@@ -1185,11 +1253,13 @@ __global__ void __launch_bounds__(256) kb_rb_resid(Bt<T> B, GateSpec gs)
     const GMEM T* b = D.cr + F.org;
     const GMEM T* x = D.cz + F.org;
     GMEM T* r = D.r0 + F.org;
-    uint32_t cc[kPlanesRB][1];
-    const bool uncut = rb_codes<1>(vb, R, F, code, 0, cc);
+    by_planes(R.pl, [&](auto PL) {
+    constexpr int P = decltype(PL)::value;
+    uint32_t cc[P][1];
+    const bool uncut = rb_codes<P, 1>(vb, R, F, code, 0, cc);
     auto body = [&](auto U) {
 #pragma unroll
-        for (int p = 0; p < kPlanesRB; ++p) {
+        for (int p = 0; p < P; ++p) {
             int i, j, m;
             if (!rb_slot(vb, R, p, i, j, m)) continue;
             const int k = rb_node(R, i, j, 0, m);
@@ -1204,6 +1274,7 @@ __global__ void __launch_bounds__(256) kb_rb_resid(Bt<T> B, GateSpec gs)
         body(std::true_type{});
     else
         body(std::false_type{});
+    });
 }
 
 // x += P e at the red nodes of level 0 from level 1 (the black half-sweep that follows
@@ -1221,14 +1292,16 @@ __global__ void __launch_bounds__(256) kb_rb_prolong(Bt<T> B, GateSpec gs)
     const Grid gc = D.lv[1].g;
     const GMEM T* __restrict__ ec = D.lv[1].x;
     GMEM T* x = D.cz + F.org;
+    by_planes(R.pl, [&](auto PL) {
 #pragma unroll
-    for (int p = 0; p < kPlanesRB; ++p) {
+    for (int p = 0; p < decltype(PL)::value; ++p) {
         int i, j, m;
         if (!rb_slot(vb, R, p, i, j, m)) continue;
         const int k = rb_node(R, i, j, 0, m);
         if (k < 0) continue;
         stf(x, rb_rel(R, F, i, j, 0, m)) += prolong_at(gc, ec, i, j, k);
     }
+    });
 }
 
 // ---- CG over the level-0 unknowns ----------------------------------------------------------
@@ -1269,12 +1342,14 @@ __global__ void __launch_bounds__(256) kb_rb_apply(Bt<T> B)
     GMEM T* q = D.cq + F.org;
     const T beta = (T)st->beta;
     auto pd = [&](uint32_t f) { return ldf(z, f) + beta * ldf(po, f); };
-    uint32_t cc[kPlanesRB][2];
-    const bool uncut = rb_codes<2>(vb, R, F, code, 0, cc);
     double v[1] = {0.0};
+    by_planes(R.pl, [&](auto PL) {
+    constexpr int P = decltype(PL)::value;
+    uint32_t cc[P][2];
+    const bool uncut = rb_codes<P, 2>(vb, R, F, code, 0, cc);
     auto body = [&](auto U) {
 #pragma unroll
-        for (int p = 0; p < kPlanesRB; ++p) {
+        for (int p = 0; p < P; ++p) {
             int i, j, m;
             if (!rb_slot(vb, R, p, i, j, m)) continue;
 #pragma unroll
@@ -1295,6 +1370,7 @@ __global__ void __launch_bounds__(256) kb_rb_apply(Bt<T> B)
         body(std::true_type{});
     else
         body(std::false_type{});
+    });
     bsum(v, 1, sh);
     if (threadIdx.x == 0) D.part[local] = v[0];
 }
@@ -1319,8 +1395,9 @@ __global__ void __launch_bounds__(256) kb_rb_update(Bt<T> B)
     const GMEM T* q = D.cq + F.org;
     const T a = (T)st->alpha;
     double v[1] = {0.0};
+    by_planes(R.pl, [&](auto PL) {
 #pragma unroll
-    for (int pl = 0; pl < kPlanesRB; ++pl) {
+    for (int pl = 0; pl < decltype(PL)::value; ++pl) {
         int i, j, m;
         if (!rb_slot(vb, R, pl, i, j, m)) continue;
         for (int c = 0; c < 2; ++c) {
@@ -1335,6 +1412,7 @@ __global__ void __launch_bounds__(256) kb_rb_update(Bt<T> B)
             v[0] += (double)rv * (double)rv;
         }
     }
+    });
     bsum(v, 1, sh);
     if (threadIdx.x == 0) D.part[D.nb + local] = v[0];
 }
@@ -1354,8 +1432,9 @@ __global__ void __launch_bounds__(256) kb_rb_dot(Bt<T> B, GateSpec gs)
     const GMEM T* r = D.cr + F.org;
     const GMEM T* z = D.cz + F.org;
     double v[1] = {0.0};
+    by_planes(R.pl, [&](auto PL) {
 #pragma unroll
-    for (int pl = 0; pl < kPlanesRB; ++pl) {
+    for (int pl = 0; pl < decltype(PL)::value; ++pl) {
         int i, j, m;
         if (!rb_slot(vb, R, pl, i, j, m)) continue;
         for (int c = 0; c < 2; ++c) {
@@ -1364,6 +1443,7 @@ __global__ void __launch_bounds__(256) kb_rb_dot(Bt<T> B, GateSpec gs)
             v[0] += (double)ldf(r, e) * (double)ldf(z, e);
         }
     }
+    });
     bsum(v, 1, sh);
     if (threadIdx.x == 0) D.part[local] = v[0];
 }
@@ -1379,8 +1459,9 @@ __global__ void __launch_bounds__(256) kb_rb_fold(Bt<T> B, int force)
     if (!force && D.st->status != 3) return;
     const RB R = D.rb;
     const VB vb = vb_rb(R, local, D.nb);
+    by_planes(R.pl, [&](auto PL) {
 #pragma unroll
-    for (int p = 0; p < kPlanesRB; ++p) {
+    for (int p = 0; p < decltype(PL)::value; ++p) {
         int i, j, m;
         if (!rb_slot(vb, R, p, i, j, m)) continue;
         for (int c = 0; c < 2; ++c) {
@@ -1391,6 +1472,7 @@ __global__ void __launch_bounds__(256) kb_rb_fold(Bt<T> B, int force)
             D.cx[e] = (T)0;
         }
     }
+    });
 }
 
 // r = b - A x in FP64 from the natural-layout solution, right-hand side and codes, stored in
@@ -1411,8 +1493,9 @@ __global__ void __launch_bounds__(256) kb_rb_true_res(Bt<T> B, int force)
     const GMEM double* __restrict__ x = D.x64;
     const int64_t sx = (int64_t)g.ny * g.S, sy = g.S;
     double v[1] = {0.0};
+    by_planes(R.pl, [&](auto PL) {
 #pragma unroll
-    for (int p = 0; p < kPlanesRB; ++p) {
+    for (int p = 0; p < decltype(PL)::value; ++p) {
         int i, j, m;
         if (!rb_slot(vb, R, p, i, j, m)) continue;
         for (int c = 0; c < 2; ++c) {
@@ -1432,6 +1515,7 @@ __global__ void __launch_bounds__(256) kb_rb_true_res(Bt<T> B, int force)
             v[0] += rv * rv;
         }
     }
+    });
     bsum(v, 1, sh);
     if (threadIdx.x == 0) D.part[2 * D.nb + local] = v[0];
 }
@@ -1610,8 +1694,7 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_rb_diag0(Grid g, RB r, Op0<T> op, T* __restrict__ dinv)
 {
     const VB vb = vb_rb(r, (int)blockIdx.x, (int)gridDim.x);
-#pragma unroll
-    for (int p = 0; p < kPlanesRB; ++p) {
+    for (int p = 0; p < r.pl; ++p) {
         int i, j, m;
         if (!rb_slot(vb, r, p, i, j, m)) continue;
         for (int c = 0; c < 2; ++c) {
@@ -1631,8 +1714,7 @@ __global__ void __launch_bounds__(256) k_rb_convert(Grid g, RB r, T* __restrict_
 {
     if (gated_out(gs, gmem(st))) return;
     const VB vb = vb_rb(r, (int)blockIdx.x, (int)gridDim.x);
-#pragma unroll
-    for (int p = 0; p < kPlanesRB; ++p) {
+    for (int p = 0; p < r.pl; ++p) {
         int i, j, m;
         if (!rb_slot(vb, r, p, i, j, m)) continue;
         for (int c = 0; c < 2; ++c) {
@@ -2014,7 +2096,7 @@ MGDev<T> describe(const pb_problem* pb)
     const pb_params& P = pb->prm;
     MGDev<T> d;
     memset((void*)&d, 0, sizeof d);
-    d.rb = rb_of(pb->g);
+    d.rb = rb_tiled(pb->g);
     d.g0 = pb->g;
     const Op0<T> o = op0<T>(pb);
     d.op = OpRB<T>{gmem((const uint32_t*)G->code_rb), o.ck, o.kin, o.kout, o.mass};
@@ -2110,7 +2192,7 @@ int setup_levels(pb_problem* pb, MGData* G, hipStream_t s)
     // level 0 in the red-black layout: the codes, 1 / diagonal, the red residual and the CG
     // vectors r, z, p (two), q and the correction x (x and b of level 0 are z and r)
     const Grid& g0 = pb->g;
-    const RB rb = rb_of(g0);
+    const RB rb = rb_tiled(g0);
     G->Sh = rb.Sh;
     G->Nrb = rb.N;
     G->code_rb = (uint32_t*)pb->mem.get(sizeof(uint32_t) * (size_t)rb.N);
@@ -2327,7 +2409,7 @@ template <typename T>
 void vcycle_natural(pb_problem* pb, hipStream_t s, const CGState* st)
 {
     MGData* G = pb->mg;
-    const RB rb = rb_of(pb->g);
+    const RB rb = rb_tiled(pb->g);
     const GateSpec gs{gmem(st), 3};
     k_rb_convert<T><<<G->nb, 256, 0, s>>>(pb->g, rb, (T*)G->nat_b, (T*)G->cr, 1, gs, nullptr);
     run_vcycle<T>(s, solo_plan(pb), gs);
@@ -2504,7 +2586,7 @@ int pbi_mg_vcycle_test(pb_problem* pb, const double* r_host, double* z_host)
     int rc = pbi_mg_begin(pb, s);
     if (rc) return rc;
     MGData* G = pb->mg;
-    const RB rb = rb_of(g);
+    const RB rb = rb_tiled(g);
     const GateSpec gate{nullptr, 2};
     std::vector<double> r64((size_t)rb.N, 0.0), z64((size_t)rb.N, 0.0);
     for (int i = 1; i < g.nx - 1; ++i)
