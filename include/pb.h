@@ -95,8 +95,9 @@ typedef struct {
                                may drop by this factor before an FP64 true-residual update */
     int32_t max_iter;       /* bound on launched CG iterations */
     int32_t tile_planes;    /* planes per x-chunk of the iteration kernel's tiles: 0 = chosen
-                               from the grid (short chunks on small grids, so that a solve
-                               alone still spreads over the GPU; the serving loop takes 32
+                               from the grid (short chunks on small grids, or small blocks
+                               in place of the chunks where the vectors stay in cache, so that
+                               a solve alone still spreads over the GPU; the serving loop takes 32
                                instead, as its launches hold many problems), else a multiple
                                of 4 in [4, 128].  It changes only the summation order of the
                                reductions: a problem gives bit-identical results with the

@@ -159,9 +159,15 @@ int run_cg(pb_problem* pb, const CGBufs<T>& B, int max_iter, bool mixed, CGState
                 HIPCHK(hipEventCreate(&e2));
                 HIPCHK(hipEventRecord(e0, s));
             }
-            HIPCHK(launch_cg_iter<T>(s, pb->g, pb->ts, B, pb->cf));
-            if (sample) HIPCHK(hipEventRecord(e1, s));
-            HIPCHK(launch_cg_tail(s, B.part, B.nb, B.st));
+            if (pb->small.items) {
+                HIPCHK(launch_cg_small<T>(s, pb->g, pb->small, B, pb->cf, t));
+                if (sample) HIPCHK(hipEventRecord(e1, s));
+                if (t == n - 1) HIPCHK(launch_cg_tail(s, B.part, pb->small.items, 5 * pb->small.items, B.st));
+            } else {
+                HIPCHK(launch_cg_iter<T>(s, pb->g, pb->ts, B, pb->cf));
+                if (sample) HIPCHK(hipEventRecord(e1, s));
+                HIPCHK(launch_cg_tail(s, B.part, B.nb, 0, B.st));
+            }
             if (sample) {
                 HIPCHK(hipEventRecord(e2, s));
                 evs.push_back(e0);
@@ -865,7 +871,9 @@ int pbi_build_continue(pb_problem* pb)
     // solver scalars and partial sums
     pb->nb = pb->ts.items;
     pb->nbres = residual_blocks(g);
-    pb->part = dalloc<double>(pb, 5 * (size_t)pb->nb, &rc);
+    if (prm->precond == PB_PRECOND_JACOBI && prm->tile_planes == 0)
+        pb->small = small_shape(g, prm->precision == PB_MIXED ? (int)sizeof(float) : (int)sizeof(double));
+    pb->part = dalloc<double>(pb, 5 * (size_t)std::max(pb->nb, 2 * pb->small.items), &rc);
     CK(rc);
     pb->part_res = dalloc<double>(pb, 3 * (size_t)pb->nbres, &rc);
     CK(rc);

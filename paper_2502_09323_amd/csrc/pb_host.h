@@ -200,6 +200,7 @@ struct pb_problem {
     int64_t na;
     pbk::Grid g;
     pbk::TileShape ts;
+    pbk::SmallShape small;             // set where a solve on its own takes the small-grid iteration
     pbk::Coef cf;
     double lB, kD;
     double ctr[3] = {0.0, 0.0, 0.0};   // centre of the atoms' bounding box (Atoms::cx, cy, cz)

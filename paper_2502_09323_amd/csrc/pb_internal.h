@@ -111,6 +111,7 @@ struct CGState {
     int iter_count;    // completed iteration kernels; its parity selects the buffers
     int ru;            // 1 while a reliable update is in progress
     int n_ru;          // reliable updates done
+    int chunk0;        // small grids: iter_count at the start of the chunk of launches
 };
 
 struct TileShape {     // tiling of the interior for the stencil kernel
@@ -238,7 +239,18 @@ hipError_t launch_cg_init(hipStream_t s, const Grid& g, const CGBufs<T>& B, Coef
 hipError_t launch_cg_fin(hipStream_t s, const double* part, int nb, CGState* st, double rtol2);
 template <typename T>
 hipError_t launch_cg_iter(hipStream_t s, const Grid& g, const TileShape& ts, const CGBufs<T>& B, Coef c);
-hipError_t launch_cg_tail(hipStream_t s, const double* part, int nb, CGState* st);
+// alt: 0, or how far the sums of odd iterations lie behind those of even ones
+hipError_t launch_cg_tail(hipStream_t s, const double* part, int nb, int alt, CGState* st);
+// Small grids: one launch per iteration, which closes the iteration before it itself.  B.part holds
+// two sets of 5 * items partial sums, by the parity of the iteration; t: position in its chunk (at 0
+// the scalars and the iteration's number come from the state).
+struct SmallShape {
+    int nkt = 0, njt = 0, items = 0;   // tiles along z and y, all tiles (0: not used)
+    int per = 0;                       // nodes per thread
+};
+SmallShape small_shape(const Grid& g, int elem);   // elem: bytes of the iteration's numbers
+template <typename T>
+hipError_t launch_cg_small(hipStream_t s, const Grid& g, const SmallShape& ss, const CGBufs<T>& B, Coef c, int t);
 hipError_t launch_stream_copy(hipStream_t s, const void* a, void* b, size_t bytes);
 
 // everything a batched launch needs to act for one problem

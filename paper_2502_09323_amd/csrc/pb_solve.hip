@@ -309,6 +309,48 @@ __global__ void __launch_bounds__(64 * NWV) k_cg_iter(Grid g, TileShape ts, CGBu
     iter_body(g, ts, B, cf, (int)blockIdx.x);
 }
 
+// what an iteration's sums (p.q, r.z, r.r, z.q, q.D^-1 q) give the next one: alpha and beta, and the
+// status (not 0: the iteration stops)
+struct Step {
+    double alpha, beta;
+    int status;
+    bool finite;
+};
+
+__device__ __forceinline__ Step next_step(const double (&v)[5], double stop2, int stop_status)
+{
+    const double pq = v[0], gm = v[1], rr = v[2], zq = v[3], qq = v[4];
+    Step s{0.0, 0.0, 0, isfinite(pq) && isfinite(gm) && isfinite(rr) && isfinite(zq) && isfinite(qq)};
+    if (!s.finite) {
+        s.status = 2;
+        return s;
+    }
+    if (pq > 0.0 && gm > 0.0) {
+        s.alpha = gm / pq;
+        const double gn = (gm - 2.0 * s.alpha * zq) + s.alpha * s.alpha * qq;
+        s.beta = gn > 0.0 ? gn / gm : 0.0;
+    }
+    s.status = rr <= stop2 ? stop_status : !(pq > 0.0) ? 2 : 0;
+    return s;
+}
+
+// the state after iteration it (one thread)
+__device__ __forceinline__ void write_step(const Step& s, const double (&v)[5], int it, CGState* st)
+{
+    st->iter_count = it + 1;
+    st->rr = v[2];
+    st->pq = v[0];
+    if (s.finite) {
+        st->alpha = s.alpha;
+        st->beta = s.beta;
+        st->gamma = v[1];
+    }
+    if (s.status != 0) {
+        st->status = s.status;
+        st->iters = it;
+    }
+}
+
 // one block: reduce the iteration's partial sums and set the scalars of the next iteration
 __device__ __forceinline__ void tail_body(const double* __restrict__ part, int nb, CGState* st)
 {
@@ -320,37 +362,220 @@ __device__ __forceinline__ void tail_body(const double* __restrict__ part, int n
         for (int u = 0; u < 5; ++u) v[u] += part[(int64_t)u * nb + t];
     block_sum<5>(v, sh);
     if (threadIdx.x != 0) return;
-    const double pq = v[0], gm = v[1], rr = v[2], zq = v[3], qq = v[4];
     const int it = st->iter_count;
-    st->iter_count = it + 1;
-    st->rr = rr;
-    st->pq = pq;
-    if (!isfinite(pq) || !isfinite(gm) || !isfinite(rr) || !isfinite(zq) || !isfinite(qq)) {
-        st->status = 2;
-        st->iters = it;
-        return;
-    }
-    double alpha = 0.0, beta = 0.0;
-    if (pq > 0.0 && gm > 0.0) {
-        alpha = gm / pq;
-        const double gn = (gm - 2.0 * alpha * zq) + alpha * alpha * qq;
-        beta = gn > 0.0 ? gn / gm : 0.0;
-    }
-    st->alpha = alpha;
-    st->beta = beta;
-    st->gamma = gm;
-    if (rr <= st->stop2) {
-        st->status = st->stop_status;
-        st->iters = it;
-    } else if (!(pq > 0.0)) {
-        st->status = 2;
-        st->iters = it;
-    }
+    const Step s = next_step(v, st->stop2, st->stop_status);
+    write_step(s, v, it, st);
 }
 
-__global__ void __launch_bounds__(256) k_cg_tail(const double* __restrict__ part, int nb, CGState* st)
+// alt: distance of the odd iterations' partial sums from the even ones' (0: one set)
+__global__ void __launch_bounds__(256) k_cg_tail(const double* __restrict__ part, int nb, int alt, CGState* st)
 {
-    tail_body(part, nb, st);
+    tail_body(part + (st->iter_count & 1) * alt, nb, st);
+}
+
+// ---- small grids -----------------------------------------------------------------------------
+// While its vectors stay in the last-level cache, an iteration is a chain of latencies: the marching
+// kernel's planes one after the other on a part of the device, then the tail's launch.  Here one
+// launch is one iteration: a block takes 4 NX x 4 rows of 32 nodes, a thread NX nodes.  Every load
+// of the block's nodes and their halo is issued at once, and while they are on their way the block
+// reduces the partial sums of the iteration before (two sets, by parity) and takes the scalar step
+// itself.  All blocks reduce the same numbers in the same order, so they agree; block 0 writes the
+// state.  The first launch of a chunk takes its scalars and its number from the state, which no
+// block of it changes but for chunk0, and the chunk's last iteration is closed by k_cg_tail.  Same
+// recurrences as iter_body; the sums in another order.
+// Per iteration in us (FP64 | mixed, before -> now): 33^3 14.8 -> 6.9 | 14.2 -> 7.8, 65^3 15.0 ->
+// 8.5 | 13.9 -> 8.5, 97^3 25.3 -> 17.8 | 17.6 -> 13.9, 129^3 44.9 -> 34.6 | 30.1 -> 25.7, 145^3
+// 65.3 -> 52.3 | 43.5 -> 39.0.  At 65^3 what is left is launch, one round of loads, two block
+// reductions and the store; from 113^3 on it is cache bandwidth.
+constexpr int SM_Y = 4, SM_T = 512;
+
+// v plus the lane value that the DPP control CTRL brings (0 where it brings none)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
+
+// sum over groups of 8 lanes, in the last lane of each; over the wave, in lane 63
+__device__ __forceinline__ double sum8(double v)
+{
+    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);   // row_shr:2
+    return dpp_add<0x114, 0xf>(v);   // row_shr:4
+}
+__device__ __forceinline__ double sum64(double v)
+{
+    v = dpp_add<0x118, 0xf>(sum8(v));   // row_shr:8: rows of 16
+    v = dpp_add<0x142, 0xa>(v);         // row_bcast:15
+    return dpp_add<0x143, 0xc>(v);      // row_bcast:31
+}
+
+// Five sums over a block of 8 waves.  The waves' sums are formed with DPP moves (64 lanes by
+// shuffles through LDS took longer than the iteration's arithmetic) and meet in LDS; wave 0 adds
+// them up, sum u in its lane 8 u + 7 on return.
+__device__ __forceinline__ double sum5(const double (&v)[5], double* sh)
+{
+    const int w = (int)threadIdx.x >> 6, l = (int)threadIdx.x & 63;
+#pragma unroll
+    for (int u = 0; u < 5; ++u) {
+        const double a = sum64(v[u]);
+        if (l == 63) sh[8 * u + w] = a;
+    }
+    __syncthreads();
+    return sum8(l < 40 && w == 0 ? sh[l] : 0.0);
+}
+
+template <typename T, int NX>
+__global__ void __launch_bounds__(SM_T) k_cg_small(Grid g, SmallShape ss, CGBufs<T> B, Coef cf, int t0)
+{
+    static_assert(SM_T == 512 && SM_Y == 4 && (NX & (NX - 1)) == 0, "thread layout");
+    constexpr int SM_X = 4 * NX;   // a thread's nodes are four planes apart
+    constexpr int NHX = 2 * 32 * SM_Y, NHY = 2 * 32 * SM_X, NHZ = 2 * SM_X * SM_Y, NH = NHX + NHY + NHZ;
+    constexpr int HPT = (NH + SM_T - 1) / SM_T;   // halo nodes per thread
+    __shared__ double sh[2][40], step[2];
+    __shared__ int stop;
+    __shared__ T sp[SM_X + 2][SM_Y + 2][34];
+    CGState* st = B.st;
+    if (st->status != 0) return;
+    const int it = t0 == 0 ? st->iter_count : st->chunk0 + t0;
+    const int nw = it & 1, od = nw ^ 1, tid = (int)threadIdx.x;
+    const T kin = (T)cf.kin, kout = (T)cf.kout, mass = (T)cf.mass;
+    // contiguous ranges of tiles per XCD, as in iter_body
+    const int q8 = ss.items >> 3, rem = ss.items & 7, xcd = (int)blockIdx.x & 7;
+    const int item = xcd * q8 + (xcd < rem ? xcd : rem) + ((int)blockIdx.x >> 3);
+    const int kt = item % ss.nkt, t2 = item / ss.nkt, jt = t2 % ss.njt, xt = t2 / ss.njt;
+    const int k0 = 1 + kt * 32, j0 = 1 + jt * SM_Y, i0 = 1 + xt * SM_X;
+    const int kl = tid & 31, jl = (tid >> 5) & 3, il = tid >> 7;
+    const T* __restrict__ z_o = od ? B.z[1] : B.z[0];
+    const T* __restrict__ w_o = od ? B.w[1] : B.w[0];
+    const T* __restrict__ p_o = od ? B.p[1] : B.p[0];
+    const uint32_t* __restrict__ code = B.code;
+    const T* __restrict__ ck = B.ck;
+    const uint32_t sx = (uint32_t)g.ny * (uint32_t)g.S, sy = (uint32_t)g.S;
+    // positions outside the interior are clamped onto box nodes, whose vectors are 0
+    auto node = [&](int i, int j, int k) {
+        return (uint32_t)g.idx(min(i, g.nx - 1), min(j, g.ny - 1), min(k, g.nz - 1));
+    };
+    // a slot outside the interior works on node (1, 1, 1) and stores and adds nothing
+    bool ok[NX];
+    uint32_t e[NX], cc[NX], cx[NX], cy[NX], cz[NX];
+    T oz[NX], ow[NX], op[NX], ox[NX];
+#pragma unroll
+    for (int q = 0; q < NX; ++q) {
+        const int i = i0 + il + 4 * q, j = j0 + jl, k = k0 + kl;
+        ok[q] = i <= g.nx - 2 && j <= g.ny - 2 && k <= g.nz - 2;
+        e[q] = ok[q] ? (uint32_t)g.idx(i, j, k) : (uint32_t)g.idx(1, 1, 1);
+        oz[q] = at(z_o, e[q]);
+        ow[q] = at(w_o, e[q]);
+        op[q] = at(p_o, e[q]);
+        ox[q] = at((const T*)B.x, e[q]);
+        cc[q] = at(code, e[q]);
+        cx[q] = at(code, e[q] - sx);
+        cy[q] = at(code, e[q] - sy);
+        cz[q] = at(code, e[q] - 1);
+    }
+    // the halo: planes before and after, rows before and after, the ends of the rows
+    int hl[HPT];
+    T hz[HPT], hw[HPT], hp[HPT];
+#pragma unroll
+    for (int q = 0; q < HPT; ++q) {
+        const int t = tid + q * SM_T;
+        int a, b, c;   // position in the tile with its halo
+        if (t < NHX) {
+            a = t < NHX / 2 ? 0 : SM_X + 1;
+            b = 1 + ((t >> 5) & 3);
+            c = 1 + (t & 31);
+        } else if (t < NHX + NHY) {
+            const int u = t - NHX;
+            a = 1 + ((u >> 5) & (SM_X - 1));
+            b = u < NHY / 2 ? 0 : SM_Y + 1;
+            c = 1 + (u & 31);
+        } else {
+            const int u = t - NHX - NHY;
+            a = 1 + ((u >> 2) & (SM_X - 1));
+            b = 1 + (u & 3);
+            c = u < NHZ / 2 ? 0 : 33;
+        }
+        hl[q] = t < NH ? (a * (SM_Y + 2) + b) * 34 + c : -1;
+        const uint32_t h = t < NH ? node(i0 - 1 + a, j0 - 1 + b, k0 - 1 + c) : e[0];
+        hz[q] = at(z_o, h);
+        hw[q] = at(w_o, h);
+        hp[q] = at(p_o, h);
+    }
+    // the step of the iteration before
+    T aT, bT;
+    if (t0 == 0) {
+        aT = (T)st->alpha;
+        bT = (T)st->beta;
+        if (blockIdx.x == 0 && tid == 0) st->chunk0 = it;
+    } else {
+        const double* part = B.part + (int64_t)od * 5 * ss.items;
+        double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        for (int t = tid; t < ss.items; t += SM_T)
+#pragma unroll
+            for (int u = 0; u < 5; ++u) v[u] += part[(int64_t)u * ss.items + t];
+        const double r = sum5(v, sh[0]);
+        if (tid < 64) {
+            // every lane of wave 0 gets the five sums, and thread 0 takes the step
+            double tot[5];
+#pragma unroll
+            for (int u = 0; u < 5; ++u)
+                tot[u] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(r), 8 * u + 7),
+                                          __builtin_amdgcn_readlane(__double2loint(r), 8 * u + 7));
+            if (tid == 0) {
+                const Step s = next_step(tot, st->stop2, st->stop_status);
+                if (blockIdx.x == 0) write_step(s, tot, it - 1, st);
+                step[0] = s.alpha;
+                step[1] = s.beta;
+                stop = s.status;
+            }
+        }
+        __syncthreads();
+        if (stop != 0) return;
+        aT = (T)step[0];
+        bT = (T)step[1];
+    }
+    T zv[NX], p0[NX];
+#pragma unroll
+    for (int q = 0; q < NX; ++q) {
+        zv[q] = oz[q] - aT * ow[q];
+        p0[q] = zv[q] + bT * op[q];
+        sp[1 + il + 4 * q][1 + jl][1 + kl] = ok[q] ? p0[q] : (T)0;
+    }
+#pragma unroll
+    for (int q = 0; q < HPT; ++q)
+        if (hl[q] >= 0) (&sp[0][0][0])[hl[q]] = (hz[q] - aT * hw[q]) + bT * hp[q];
+    __syncthreads();
+    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < NX; ++q) {
+        const int l = 1 + il + 4 * q;
+        const T Kxm = edgeK(cx[q], 0, ck, kin, kout), Kxp = edgeK(cc[q], 0, ck, kin, kout);
+        const T Kym = edgeK(cy[q], 1, ck, kin, kout), Kyp = edgeK(cc[q], 1, ck, kin, kout);
+        const T Kzm = edgeK(cz[q], 2, ck, kin, kout), Kzp = edgeK(cc[q], 2, ck, kin, kout);
+        const T D = diag_sum(Kxm, Kxp, Kym, Kyp, Kzm, Kzp, (cc[q] & C_SOLUTE) ? (T)0 : mass);
+        const T nbs = Kxm * sp[l - 1][1 + jl][1 + kl] + Kxp * sp[l + 1][1 + jl][1 + kl] + Kym * sp[l][jl][1 + kl] +
+                      Kyp * sp[l][2 + jl][1 + kl] + Kzm * sp[l][1 + jl][kl] + Kzp * sp[l][1 + jl][2 + kl];
+        const T qv = D * p0[q] - nbs;
+        const T wq = qv / D;
+        if (ok[q]) {
+            at(nw ? B.z[1] : B.z[0], e[q]) = zv[q];
+            at(nw ? B.w[1] : B.w[0], e[q]) = wq;
+            at(nw ? B.p[1] : B.p[0], e[q]) = p0[q];
+            at(B.x, e[q]) = ox[q] + aT * op[q];
+            const double dD = (double)D, dz = (double)zv[q], dw = (double)wq, dq = (double)qv, dzD = dD * dz,
+                         dwD = dD * dw;
+            acc[0] += (double)p0[q] * dq;
+            acc[1] += dzD * dz;
+            acc[2] += dzD * dzD;
+            acc[3] += dzD * dw;
+            acc[4] += dwD * dw;
+        }
+    }
+    const double r = sum5(acc, sh[1]);
+    if (tid < 40 && (tid & 7) == 7) B.part[((int64_t)nw * 5 + (tid >> 3)) * ss.items + blockIdx.x] = r;
 }
 
 template <typename T>
@@ -713,9 +938,47 @@ hipError_t launch_cg_iter(hipStream_t s, const Grid& g, const TileShape& ts, con
     return hipGetLastError();
 }
 
-hipError_t launch_cg_tail(hipStream_t s, const double* part, int nb, CGState* st)
+// One launch per iteration while the iteration's vectors (z, w, p twice, x) and codes stay in the
+// last-level cache (256 MB) with what else lives there: at 161^3 in FP64 (250 MB) both forms take
+// 78 us, at 193^3 131 (marching) against 158, as the halos of the small tiles then come from memory;
+// in FP32 145^3 (98 MB) 39.0 against 43.5 and 177^3 (177 MB) 66 against 68.
+constexpr int64_t kSmallBytes = (int64_t)200 << 20;
+
+// Nodes per thread: one while a block per CU covers the grid (33^3: 6.9 us, with two 7.6; 49^3, more
+// blocks than that, 8.2 and 7.9), two while all blocks of that size run at once (three per CU; 81^3
+// 14.3 us, with four 15.6), and four above, where halo traffic counts (97^3: 17.6, with two 19.0;
+// 129^3: 34.4 and 37.9).
+SmallShape small_shape(const Grid& g, int elem)
 {
-    k_cg_tail<<<1, 256, 0, s>>>(part, nb, st);
+    SmallShape t;
+    if (g.N * (7 * elem + 4) > kSmallBytes) return t;
+    t.nkt = (g.nz - 2 + 31) / 32;
+    t.njt = (g.ny - 2 + SM_Y - 1) / SM_Y;
+    auto tiles = [&](int n) { return t.nkt * t.njt * ((g.nx - 2 + 4 * n - 1) / (4 * n)); };
+    t.per = tiles(1) <= 256 ? 1 : tiles(2) <= 768 ? 2 : 4;
+    t.items = tiles(t.per);
+    return t;
+}
+
+template <typename T>
+hipError_t launch_cg_small(hipStream_t s, const Grid& g, const SmallShape& ss, const CGBufs<T>& B, Coef c, int t)
+{
+    if (ss.per == 1)
+        k_cg_small<T, 1><<<ss.items, SM_T, 0, s>>>(g, ss, B, c, t);
+    else if (ss.per == 2)
+        k_cg_small<T, 2><<<ss.items, SM_T, 0, s>>>(g, ss, B, c, t);
+    else
+        k_cg_small<T, 4><<<ss.items, SM_T, 0, s>>>(g, ss, B, c, t);
+    return hipGetLastError();
+}
+
+template hipError_t launch_cg_small<double>(hipStream_t, const Grid&, const SmallShape&, const CGBufs<double>&, Coef,
+                                            int);
+template hipError_t launch_cg_small<float>(hipStream_t, const Grid&, const SmallShape&, const CGBufs<float>&, Coef, int);
+
+hipError_t launch_cg_tail(hipStream_t s, const double* part, int nb, int alt, CGState* st)
+{
+    k_cg_tail<<<1, 256, 0, s>>>(part, nb, alt, st);
     return hipGetLastError();
 }
 
