@@ -52,10 +52,11 @@ inline unsigned nblk(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); 
 
 __device__ __forceinline__ void decode(const Grid& g, int64_t e, int& i, int& j, int& k)
 {
-    const int64_t row = e / g.S;
-    k = (int)(e - row * g.S) - Z0;
-    j = (int)(row % g.ny);
-    i = (int)(row / g.ny);
+    // 32-bit divisions: a grid holds at most 2^29 elements
+    const uint32_t u = (uint32_t)e, row = u / (uint32_t)g.S, r2 = row / (uint32_t)g.ny;
+    k = (int)(u - row * (uint32_t)g.S) - Z0;
+    j = (int)(row - r2 * (uint32_t)g.ny);
+    i = (int)r2;
 }
 
 struct Cells {             // refinement flags of the coarse cells
@@ -324,6 +325,33 @@ __global__ void __launch_bounds__(256) k_lift(Grid g, const double* __restrict__
 
 // ---- operator and CG ---------------------------------------------------------------------
 
+__device__ __forceinline__ void bsum(double* v, int nv, double* sh)
+{
+    for (int t = 0; t < nv; ++t)
+        for (int o = 32; o > 0; o >>= 1) v[t] += __shfl_xor(v[t], o, 64);
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    __syncthreads();
+    if (l == 0)
+        for (int t = 0; t < nv; ++t) sh[4 * t + w] = v[t];
+    __syncthreads();
+    for (int t = 0; t < nv; ++t) v[t] = (sh[4 * t] + sh[4 * t + 1]) + (sh[4 * t + 2] + sh[4 * t + 3]);
+}
+
+// The kernels over both grids run in one launch: blocks [0, nbc) take the coarse grid, the others
+// the fine sub-lattice.  (Blocks that walk an eighth of the grid per XCD, for the stencil's planes in
+// that XCD's L2, took 10 to 20 % longer: the unknowns lie unevenly over the eighths.)
+struct Split {
+    int64_t Nc, Nf;
+    int nbc;
+    const uint8_t *rc, *rf;
+    __device__ bool coarse() const { return (int)blockIdx.x < nbc; }
+    __device__ int64_t n() const { return coarse() ? Nc : Nf; }
+    __device__ int64_t first() const { return (coarse() ? blockIdx.x : blockIdx.x - nbc) * (int64_t)256 + threadIdx.x; }
+    __device__ int64_t end() const { return n(); }
+    __device__ int64_t stride() const { return (coarse() ? nbc : (int)gridDim.x - nbc) * (int64_t)256; }
+    __device__ const uint8_t* role() const { return coarse() ? rc : rf; }
+};
+
 // derived fine values from the coarse ones
 template <typename T>
 __global__ void __launch_bounds__(256) k_fill(int64_t ng, const int64_t* __restrict__ gfine,
@@ -338,52 +366,118 @@ __global__ void __launch_bounds__(256) k_fill(int64_t ng, const int64_t* __restr
     vf[gfine[t]] = s / (T)np;
 }
 
-// q = (cell contributions of this grid) p at every node with a role; 0 elsewhere
+constexpr double kOmega = 0.8;   // smoother damping of the two-level preconditioner: w D^-1 A stays below 2
+
+__device__ __forceinline__ bool stopped(const CGState* st) { return st && st->status != 0; }
+
+// What a pass over the operator leaves, with a = (cell contributions of a node's own grid) v:
+//   OP_RAW   o = a
+//   OP_DOT   o = a, and partial sums of v.a over the unknowns
+//   OP_RES   o = r - a at the unknowns, -a at the derived fine nodes (0 elsewhere, as above)
+//   OP_POST  o = v + w D^-1 (r - a) at the unknowns (the second smoothing step), a at the derived
+//            nodes, and partial sums of r.o over the unknowns
+// In OP_RAW, OP_DOT and OP_POST the rows of the derived nodes are still to be added to their coarse
+// parents (k_restrict, which also corrects the sums); after OP_RES the restriction to the coarse
+// grid does it (k_rest_h).  The passes over the vectors that followed the operator (a dot product,
+// r - q, the smoothing step) took a fifth of an iteration on a mixed 193^3 problem.
+enum { OP_RAW, OP_DOT, OP_RES, OP_POST };
+
 template <typename T>
-__global__ void __launch_bounds__(256) k_apply(Grid g, const T* __restrict__ K, const uint8_t* __restrict__ role,
-                                               const T* __restrict__ p, T* __restrict__ q, const CGState* st)
+struct OpArgs {
+    const T *Kc, *Kf, *vc, *vf;
+    T *oc, *of;
+    const T *rc, *rf, *dc, *df;   // residual (OP_RES, OP_POST) and D^-1 (OP_POST)
+};
+
+// Bound by HBM: four coefficients, v, the role and the result per node.
+template <typename T, int MODE>
+__global__ void __launch_bounds__(256) k_apply(Split sp, int64_t sxc, int64_t syc, int64_t sxf, int64_t syf,
+                                               OpArgs<T> A, double* part, const CGState* st)
 {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= g.N || (st && st->status != 0)) return;
-    if (!role[e]) {
-        q[e] = (T)0;
-        return;
+    __shared__ double sh[4];
+    if (stopped(st)) return;
+    const bool coarse = sp.coarse();
+    const uint8_t* __restrict__ role = sp.role();
+    const T* __restrict__ K = coarse ? A.Kc : A.Kf;
+    const T* __restrict__ p = coarse ? A.vc : A.vf;
+    const T* __restrict__ r = coarse ? A.rc : A.rf;
+    const T* __restrict__ d = coarse ? A.dc : A.df;
+    T* __restrict__ o = coarse ? A.oc : A.of;
+    const int64_t N = sp.n(), sx = coarse ? sxc : sxf, sy = coarse ? syc : syf;
+    double v[1] = {0.0};
+    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) {
+        const int ro = role[e];
+        if (!ro) {
+            o[e] = (T)0;
+            continue;
+        }
+        const T kxp = K[e], kxm = K[e - sx], kyp = K[N + e], kym = K[N + e - sy];
+        const T kzp = K[2 * N + e], kzm = K[2 * N + e - 1];
+        const T D = ((kxp + kxm) + (kyp + kym)) + ((kzp + kzm) + K[3 * N + e]);
+        const T p0 = p[e];
+        const T a = D * p0 - (((kxm * p[e - sx] + kxp * p[e + sx]) + (kym * p[e - sy] + kyp * p[e + sy])) +
+                              (kzm * p[e - 1] + kzp * p[e + 1]));
+        if (MODE == OP_RES) {
+            o[e] = (ro == 1 ? r[e] : (T)0) - a;
+        } else if (MODE == OP_POST && ro == 1) {
+            const T rv = r[e], zv = p0 + (T)kOmega * d[e] * (rv - a);
+            o[e] = zv;
+            v[0] += (double)rv * (double)zv;
+        } else {
+            o[e] = a;
+            if (MODE == OP_DOT && ro == 1) v[0] += (double)p0 * (double)a;
+        }
     }
-    const int64_t sx = (int64_t)g.ny * g.S, sy = g.S;
-    const T kxp = K[e], kxm = K[e - sx], kyp = K[g.N + e], kym = K[g.N + e - sy];
-    const T kzp = K[2 * g.N + e], kzm = K[2 * g.N + e - 1];
-    const T D = ((kxp + kxm) + (kyp + kym)) + ((kzp + kzm) + K[3 * g.N + e]);
-    q[e] = D * p[e] - (((kxm * p[e - sx] + kxp * p[e + sx]) + (kym * p[e - sy] + kyp * p[e + sy])) +
-                       (kzm * p[e - 1] + kzp * p[e + 1]));
+    if (MODE == OP_DOT || MODE == OP_POST) {
+        bsum(v, 1, sh);
+        if (threadIdx.x == 0) part[blockIdx.x] = v[0];
+    }
 }
 
 // the rows of the derived fine nodes go to their coarse parents: one thread per coarse node
 // that is a parent (rnode), gathering the derived fine nodes among the 27 fine nodes around it
 // in fine-lattice order; the derived node at 2C + d is a child of C with weight 1 / 2^(number
-// of nonzero components of d)
-template <typename T>
+// of nonzero components of d).  MODE as in k_apply; part: what this adds to its sums, per block.
+template <typename T, int MODE>
 __global__ void __launch_bounds__(256) k_restrict(int64_t nr, const int64_t* __restrict__ rnode, Grid gc, Grid gf,
                                                   const uint8_t* __restrict__ rolef, const T* __restrict__ vf,
-                                                  T* __restrict__ vc, const CGState* st)
+                                                  T* __restrict__ oc, const T* __restrict__ pc,
+                                                  const T* __restrict__ rc, const T* __restrict__ dc, double* part,
+                                                  const CGState* st)
 {
+    __shared__ double sh[4];
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= nr || (st && st->status != 0)) return;
-    const int64_t ec = rnode[t];
-    int i, j, k;
-    decode(gc, ec, i, j, k);
-    const int F[3] = {2 * i - gf.off[0], 2 * j - gf.off[1], 2 * k - gf.off[2]};
-    T s = (T)0;
-    for (int a = -1; a <= 1; ++a)
-        for (int b = -1; b <= 1; ++b)
-            for (int c = -1; c <= 1; ++c) {
-                const int f0 = F[0] + a, f1 = F[1] + b, f2 = F[2] + c;
-                if (f0 < 0 || f1 < 0 || f2 < 0 || f0 >= gf.nx || f1 >= gf.ny || f2 >= gf.nz) continue;
-                const int64_t ef = gf.idx(f0, f1, f2);
-                if (rolef[ef] < 2) continue;
-                const int np = 1 << ((a != 0) + (b != 0) + (c != 0));
-                s += (T)(1.0 / np) * vf[ef];
-            }
-    vc[ec] += s;
+    if (stopped(st)) return;
+    double v[1] = {0.0};
+    if (t < nr) {
+        const int64_t ec = rnode[t];
+        int i, j, k;
+        decode(gc, ec, i, j, k);
+        const int F[3] = {2 * i - gf.off[0], 2 * j - gf.off[1], 2 * k - gf.off[2]};
+        T s = (T)0;
+        for (int a = -1; a <= 1; ++a)
+            for (int b = -1; b <= 1; ++b)
+                for (int c = -1; c <= 1; ++c) {
+                    const int f0 = F[0] + a, f1 = F[1] + b, f2 = F[2] + c;
+                    if (f0 < 0 || f1 < 0 || f2 < 0 || f0 >= gf.nx || f1 >= gf.ny || f2 >= gf.nz) continue;
+                    const int64_t ef = gf.idx(f0, f1, f2);
+                    if (rolef[ef] < 2) continue;
+                    const int np = 1 << ((a != 0) + (b != 0) + (c != 0));
+                    s += (T)(1.0 / np) * vf[ef];
+                }
+        if (MODE == OP_POST) {
+            const T ds = (T)kOmega * dc[ec] * s;
+            oc[ec] -= ds;
+            v[0] = -(double)rc[ec] * (double)ds;
+        } else {
+            oc[ec] += s;
+            if (MODE == OP_DOT) v[0] = (double)pc[ec] * (double)s;
+        }
+    }
+    if (MODE == OP_DOT || MODE == OP_POST) {
+        bsum(v, 1, sh);
+        if (threadIdx.x == 0) part[blockIdx.x] = v[0];
+    }
 }
 
 // ---- the lists of derived fine nodes and of their coarse parents, built on the device -------
@@ -572,54 +666,15 @@ __global__ void __launch_bounds__(256) k_zero_derived(int64_t ng, const int64_t*
     if (t < ng) bf[gfine[t]] = 0.0;
 }
 
-__device__ __forceinline__ void bsum(double* v, int nv, double* sh)
-{
-    for (int t = 0; t < nv; ++t)
-        for (int o = 32; o > 0; o >>= 1) v[t] += __shfl_xor(v[t], o, 64);
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    __syncthreads();
-    if (l == 0)
-        for (int t = 0; t < nv; ++t) sh[4 * t + w] = v[t];
-    __syncthreads();
-    for (int t = 0; t < nv; ++t) v[t] = (sh[4 * t] + sh[4 * t + 1]) + (sh[4 * t + 2] + sh[4 * t + 3]);
-}
-
-// The vector kernels run over both grids in one launch: blocks [0, nbc) take the coarse
-// grid, the others the fine sub-lattice.
-struct Split {
-    int64_t Nc, Nf;
-    int nbc;
-    const uint8_t *rc, *rf;
-    __device__ bool coarse() const { return (int)blockIdx.x < nbc; }
-    __device__ int64_t first() const { return (coarse() ? blockIdx.x : blockIdx.x - nbc) * (int64_t)256 + threadIdx.x; }
-    __device__ int64_t stride() const { return (coarse() ? nbc : (int64_t)gridDim.x - nbc) * (int64_t)256; }
-    __device__ int64_t n() const { return coarse() ? Nc : Nf; }
-    __device__ const uint8_t* role() const { return coarse() ? rc : rf; }
-};
-
-// partial sums of a.b over the unknowns of both grids
-template <typename T>
-__global__ void __launch_bounds__(256) k_dot(Split sp, const T* ac, const T* bc, const T* af, const T* bf,
-                                             double* part, const CGState* st)
-{
-    __shared__ double sh[8];
-    if (st->status != 0) return;
-    const uint8_t* role = sp.role();
-    const T* a = sp.coarse() ? ac : af;
-    const T* b = sp.coarse() ? bc : bf;
-    double v[1] = {0.0};
-    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride())
-        if (role[e] == 1) v[0] += (double)a[e] * (double)b[e];
-    bsum(v, 1, sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = v[0];
-}
-
-__global__ void __launch_bounds__(256) k_alpha(const double* part, int nb, CGState* st)
+// The partial sums lie at part[0, 3 nb), nb per quantity, and those that k_restrict adds to the first
+// quantity at part[3 nb, 3 nb + nx).
+__global__ void __launch_bounds__(256) k_alpha(const double* part, int nb, int nx, CGState* st)
 {
     __shared__ double sh[8];
     if (st->status != 0) return;
     double v[1] = {0.0};
     for (int t = threadIdx.x; t < nb; t += 256) v[0] += part[t];
+    for (int t = threadIdx.x; t < nx; t += 256) v[0] += part[3 * nb + t];
     bsum(v, 1, sh);
     if (threadIdx.x == 0) {
         const double pq = v[0];
@@ -633,11 +688,12 @@ __global__ void __launch_bounds__(256) k_alpha(const double* part, int nb, CGSta
     }
 }
 
-// x += alpha p, r -= alpha q, z = D^-1 r; partial sums of r.z and r.r
+// x += alpha p, r -= alpha q, z = om D^-1 r (om: 1, or the first smoothing step's damping); partial
+// sums of r.z (read with om = 1 only) and r.r
 template <typename T>
 __global__ void __launch_bounds__(256) k_update(Split sp, T* xc, T* rrc, T* zc, const T* pc, const T* qc, const T* dc,
                                                 T* xf, T* rrf, T* zf, const T* pf, const T* qf, const T* df,
-                                                double* part, int nb, const CGState* st)
+                                                T om, double* part, int nb, const CGState* st)
 {
     __shared__ double sh[8];
     if (st->status != 0) return;
@@ -651,13 +707,13 @@ __global__ void __launch_bounds__(256) k_update(Split sp, T* xc, T* rrc, T* zc, 
     const T* d = coarse ? dc : df;
     const T a = (T)st->alpha;
     double v[2] = {0.0, 0.0};
-    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride()) {
+    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) {
         if (role[e] != 1) continue;
         x[e] += a * p[e];
         const T rv = r[e] - a * q[e];
         r[e] = rv;
         const T zv = d[e] * rv;
-        z[e] = zv;
+        z[e] = om * zv;
         v[0] += (double)rv * (double)zv;
         v[1] += (double)rv * (double)rv;
     }
@@ -672,7 +728,7 @@ __global__ void __launch_bounds__(256) k_update(Split sp, T* xc, T* rrc, T* zc, 
 // FP64 solve's goal; in mixed precision the FP32 goal) or to trig2 (mixed precision: the
 // point at which the true residual is computed again); with mode 1 the first residual sets
 // the reference norm (no beta)
-__global__ void __launch_bounds__(256) k_beta(const double* part, int nb, CGState* st, int mode, double rtol2)
+__global__ void __launch_bounds__(256) k_beta(const double* part, int nb, int nx, CGState* st, int mode, double rtol2)
 {
     __shared__ double sh[8];
     if (mode == 0 && st->status != 0) return;
@@ -681,6 +737,7 @@ __global__ void __launch_bounds__(256) k_beta(const double* part, int nb, CGStat
         v[0] += part[t];
         v[1] += part[nb + t];
     }
+    for (int t = threadIdx.x; t < nx; t += 256) v[0] += part[3 * nb + t];
     bsum(v, 2, sh);
     if (threadIdx.x == 0) {
         const double gm = v[0], rr = v[1];
@@ -706,13 +763,16 @@ __global__ void __launch_bounds__(256) k_beta(const double* part, int nb, CGStat
     }
 }
 
-// p = z + beta p over the unknowns of one grid (init: beta = 0)
+// p = z + beta p over the unknowns (init: beta = 0)
 template <typename T>
-__global__ void __launch_bounds__(256) k_pupd(int64_t N, const uint8_t* role, const T* z, T* p, const CGState* st)
+__global__ void __launch_bounds__(256) k_pupd(Split sp, const T* zc, const T* zf, T* pc, T* pf, const CGState* st)
 {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= N || st->status != 0) return;
-    p[e] = role[e] == 1 ? z[e] + (T)st->beta * p[e] : (T)0;
+    if (st->status != 0) return;
+    const uint8_t* role = sp.role();
+    const T* z = sp.coarse() ? zc : zf;
+    T* p = sp.coarse() ? pc : pf;
+    const T b = (T)st->beta;
+    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) p[e] = role[e] == 1 ? z[e] + b * p[e] : (T)0;
 }
 
 // ---- two-level preconditioner ----------------------------------------------------------------
@@ -724,39 +784,14 @@ __global__ void __launch_bounds__(256) k_pupd(int64_t N, const uint8_t* role, co
 // and the two nodes (F -+ 1)/2 with weight 1/2 along an odd one.  In the element type of the
 // CG (FP64, or FP32 in the mixed form, whose reliable updates apply it ungated: st = null).
 
-constexpr double kOmega = 0.8;   // smoother damping: w D^-1 A stays below 2 (SPD preconditioner)
-
-__device__ __forceinline__ bool stopped(const CGState* st) { return st && st->status != 0; }
-
-// z *= w at the unknowns
+// bH = I_H^T w over the coarse grid (0 on the box and the pads), w as OP_RES leaves it: the node's
+// own value plus the fine nodes among the 27 around it.  The derived ones among those hold minus
+// their row, and its share for a parent has the weight of the interpolation, so that the composite
+// residual needs no pass of its own here.  One index and fixed distances where all 27 lie in the
+// fine grid (and no role is read): 41 us against 57 at 193^3 mixed with roles and bounds.
 template <typename T>
-__global__ void __launch_bounds__(256) k_zscale(Split sp, T* zc, T* zf, const CGState* st)
-{
-    if (stopped(st)) return;
-    const uint8_t* role = sp.role();
-    T* z = sp.coarse() ? zc : zf;
-    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride())
-        if (role[e] == 1) z[e] *= (T)kOmega;
-}
-
-// q = r - q at the unknowns
-template <typename T>
-__global__ void __launch_bounds__(256) k_rsub(Split sp, const T* rc, const T* rf, T* qc, T* qf, const CGState* st)
-{
-    if (stopped(st)) return;
-    const uint8_t* role = sp.role();
-    const T* r = sp.coarse() ? rc : rf;
-    T* q = sp.coarse() ? qc : qf;
-    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride())
-        if (role[e] == 1) q[e] = r[e] - q[e];
-}
-
-// bH = I_H^T w over the coarse grid (0 on the box and the pads): the node's own value where it
-// is a coarse unknown, plus the fine unknowns among the 27 fine nodes around it
-template <typename T>
-__global__ void __launch_bounds__(256) k_rest_h(Grid gc, Grid gf, const uint8_t* __restrict__ rolec,
-                                                const uint8_t* __restrict__ rolef, const T* __restrict__ wc,
-                                                const T* __restrict__ wf, T* __restrict__ bH, const CGState* st)
+__global__ void __launch_bounds__(256) k_rest_h(Grid gc, Grid gf, const T* __restrict__ wc, const T* __restrict__ wf,
+                                                T* __restrict__ bH, const CGState* st)
 {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= gc.N || stopped(st)) return;
@@ -766,88 +801,67 @@ __global__ void __launch_bounds__(256) k_rest_h(Grid gc, Grid gf, const uint8_t*
         bH[e] = (T)0;
         return;
     }
-    T v = rolec[e] == 1 ? wc[e] : (T)0;
+    T v = wc[e];
     const int F[3] = {2 * i - gf.off[0], 2 * j - gf.off[1], 2 * k - gf.off[2]};
     const int nf[3] = {gf.nx, gf.ny, gf.nz};
-    bool near = true;
-    for (int d = 0; d < 3; ++d) near = near && F[d] >= -1 && F[d] <= nf[d];
-    if (near)
+    bool near = true, inner = true;
+    for (int d = 0; d < 3; ++d) {
+        near = near && F[d] >= -1 && F[d] <= nf[d];
+        inner = inner && F[d] >= 1 && F[d] <= nf[d] - 2;
+    }
+    if (inner) {
+        const T* __restrict__ w = wf + gf.idx(F[0], F[1], F[2]);
+        const int64_t sx = (int64_t)gf.ny * gf.S, sy = gf.S;
+        T pl[3];
+#pragma unroll
+        for (int a = -1; a <= 1; ++a) {
+            T row[3];
+#pragma unroll
+            for (int b = -1; b <= 1; ++b) {
+                const T* q = w + a * sx + b * sy;
+                row[b + 1] = q[0] + (T)0.5 * (q[-1] + q[1]);
+            }
+            pl[a + 1] = row[1] + (T)0.5 * (row[0] + row[2]);
+        }
+        v += pl[1] + (T)0.5 * (pl[0] + pl[2]);
+    } else if (near) {
         for (int a = -1; a <= 1; ++a)
             for (int b = -1; b <= 1; ++b)
                 for (int c = -1; c <= 1; ++c) {
                     const int f0 = F[0] + a, f1 = F[1] + b, f2 = F[2] + c;
                     if (f0 < 0 || f1 < 0 || f2 < 0 || f0 >= nf[0] || f1 >= nf[1] || f2 >= nf[2]) continue;
-                    const int64_t ef = gf.idx(f0, f1, f2);
-                    if (rolef[ef] != 1) continue;
                     const T w = (a ? (T)0.5 : (T)1) * (b ? (T)0.5 : (T)1) * (c ? (T)0.5 : (T)1);
-                    v += w * wf[ef];
+                    v += w * wf[gf.idx(f0, f1, f2)];
                 }
+    }
     bH[e] = v;
 }
 
-// z += I_H eH at the coarse unknowns
+// z += I_H eH at the unknowns of both grids.  A fine node takes the mean over each odd axis; along an
+// even one both of its ends are the same coarse node, so all eight are read without a branch.
 template <typename T>
-__global__ void __launch_bounds__(256) k_prol_c(int64_t N, const uint8_t* __restrict__ rolec, const T* __restrict__ eH,
-                                                T* __restrict__ zc, const CGState* st)
+__global__ void __launch_bounds__(256) k_prol(Split sp, Grid gf, Grid gc, const T* __restrict__ eH, T* zc, T* zf,
+                                              const CGState* st)
 {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= N || stopped(st)) return;
-    if (rolec[e] == 1) zc[e] += eH[e];
-}
-
-// z += I_H eH at the fine unknowns
-template <typename T>
-__global__ void __launch_bounds__(256) k_prol_f(Grid gf, Grid gc, const uint8_t* __restrict__ rolef,
-                                                const T* __restrict__ eH, T* __restrict__ zf, const CGState* st)
-{
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= gf.N || stopped(st)) return;
-    if (rolef[e] != 1) return;
-    int i, j, k;
-    decode(gf, e, i, j, k);
-    const int F[3] = {i + gf.off[0], j + gf.off[1], k + gf.off[2]};
-    T v = (T)0;
-    for (int s3 = 0; s3 < 8; ++s3) {
-        int I[3];
-        T w = (T)1;
-        bool ok = true;
-        for (int d = 0; d < 3; ++d) {
-            const int bit = (s3 >> d) & 1;
-            if (F[d] & 1) {
-                I[d] = (F[d] - 1) / 2 + bit;
-                w *= (T)0.5;
-            } else {
-                I[d] = F[d] / 2;
-                ok = ok && bit == 0;
-            }
-        }
-        if (ok) v += w * eH[gc.idx(I[0], I[1], I[2])];
-    }
-    zf[e] += v;
-}
-
-// z += w D^-1 (r - q) at the unknowns; partial sums of r.z in part[0, nb)
-template <typename T>
-__global__ void __launch_bounds__(256) k_post(Split sp, T* zc, T* zf, const T* rc, const T* rf, const T* qc,
-                                              const T* qf, const T* dc, const T* df, double* part, const CGState* st)
-{
-    __shared__ double sh[8];
     if (stopped(st)) return;
-    const bool coarse = sp.coarse();
-    const uint8_t* role = sp.role();
-    T* z = coarse ? zc : zf;
-    const T* r = coarse ? rc : rf;
-    const T* q = coarse ? qc : qf;
-    const T* d = coarse ? dc : df;
-    double v[1] = {0.0};
-    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride()) {
-        if (role[e] != 1) continue;
-        const T zv = z[e] + (T)kOmega * d[e] * (r[e] - q[e]);
-        z[e] = zv;
-        v[0] += (double)r[e] * (double)zv;
+    const uint8_t* __restrict__ role = sp.role();
+    if (sp.coarse()) {
+        for (int64_t e = sp.first(); e < sp.end(); e += sp.stride())
+            if (role[e] == 1) zc[e] += eH[e];
+        return;
     }
-    bsum(v, 1, sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = v[0];
+    const int64_t gx = (int64_t)gc.ny * gc.S, gy = gc.S;
+    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) {
+        if (role[e] != 1) continue;
+        int i, j, k;
+        decode(gf, e, i, j, k);
+        const int F0 = i + gf.off[0], F1 = j + gf.off[1], F2 = k + gf.off[2];
+        const T* __restrict__ c = eH + gc.idx(F0 >> 1, F1 >> 1, F2 >> 1);
+        const int64_t dx = (F0 & 1) ? gx : 0, dy = (F1 & 1) ? gy : 0, dz = F2 & 1;
+        const T v0 = (c[0] + c[dz]) + (c[dy] + c[dy + dz]);
+        const T v1 = (c[dx] + c[dx + dz]) + (c[dx + dy] + c[dx + dy + dz]);
+        zf[e] += (T)0.125 * (v0 + v1);
+    }
 }
 
 // ---- mixed precision: reliable updates ------------------------------------------------------
@@ -864,7 +878,7 @@ __global__ void __launch_bounds__(256) k_fold(Split sp, double* xc, float* dc, d
     double* x = sp.coarse() ? xc : xf;
     float* d = sp.coarse() ? dc : df;
     const uint8_t* role = sp.role();
-    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride())
+    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride())
         if (role[e] == 1) {
             x[e] += (double)d[e];
             d[e] = 0.0f;
@@ -882,7 +896,7 @@ __global__ void __launch_bounds__(256) k_true_res(Split sp, const double* bc, co
     const double* q = coarse ? qc : qf;
     double* r = coarse ? rc : rf;
     double v[1] = {0.0};
-    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride()) {
+    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) {
         const double rv = role[e] == 1 ? b[e] - q[e] : 0.0;
         r[e] = rv;
         v[0] += rv * rv;
@@ -891,10 +905,10 @@ __global__ void __launch_bounds__(256) k_true_res(Split sp, const double* bc, co
     if (threadIdx.x == 0) part[blockIdx.x] = v[0];
 }
 
-// r32 = r64, z32 = D^-1 r32; partial sums of r.z and r.r
+// r32 = r64, z32 = om D^-1 r32; partial sums of r.z and r.r (as in k_update)
 __global__ void __launch_bounds__(256) k_replace(Split sp, const double* r64c, float* rc, float* zc, const float* dc,
                                                  const double* r64f, float* rf, float* zf, const float* df,
-                                                 double* part, int nb)
+                                                 float om, double* part, int nb)
 {
     __shared__ double sh[8];
     const bool coarse = sp.coarse();
@@ -904,11 +918,11 @@ __global__ void __launch_bounds__(256) k_replace(Split sp, const double* r64c, f
     float* z = coarse ? zc : zf;
     const float* d = coarse ? dc : df;
     double v[2] = {0.0, 0.0};
-    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride()) {
+    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) {
         const float rv = role[e] == 1 ? (float)r64[e] : 0.0f;
         const float zv = d[e] * rv;
         r[e] = rv;
-        z[e] = zv;
+        z[e] = om * zv;
         v[0] += (double)rv * (double)zv;
         v[1] += (double)rv * (double)rv;
     }
@@ -924,7 +938,7 @@ __global__ void __launch_bounds__(256) k_replace(Split sp, const double* r64c, f
 // r = b) sets the goals.  A replacement follows a step whose direction update was skipped
 // (status 3 stops the launches after beta), so the next direction update takes beta from the
 // replaced residual.
-__global__ void __launch_bounds__(256) k_ru_fin(const double* part, int nb, CGState* st, int init, double rtol2,
+__global__ void __launch_bounds__(256) k_ru_fin(const double* part, int nb, int nx, CGState* st, int init, double rtol2,
                                                 double delta2)
 {
     __shared__ double sh[12];
@@ -934,6 +948,7 @@ __global__ void __launch_bounds__(256) k_ru_fin(const double* part, int nb, CGSt
         v[1] += part[nb + t];
         v[2] += part[2 * nb + t];
     }
+    for (int t = threadIdx.x; t < nx; t += 256) v[0] += part[3 * nb + t];
     bsum(v, 3, sh);
     if (threadIdx.x == 0) {
         const double gm = v[0], rr = v[1], rr64 = v[2];
@@ -1240,9 +1255,11 @@ int pbi_refine_build(pb_problem* pb, const double* xyz, const double* rad, const
     k_invert<<<nblk(gc.N, 256), 256, 0, s>>>(gc.N, R->rolec, R->dc);
     k_invert<<<nblk(gf.N, 256), 256, 0, s>>>(gf.N, R->rolef, R->df);
     RCHK(hipGetLastError());
-    R->nbc = (int)std::min<int64_t>(1024, (int64_t)nblk(gc.N, 256));
-    R->nbf = (int)std::min<int64_t>(1024, (int64_t)nblk(gf.N, 256));
-    R->part = (double*)pb->mem.get(sizeof(double) * 3 * (size_t)(R->nbc + R->nbf));
+    // blocks of the kernels over both grids: each grid's fill the device once (mixed 193^3 problem, whole:
+    // 512 blocks a grid 70.9 ms, 1024 61.8, 2048 60.8, 4096 62.2, 16384 66.4)
+    R->nbc = (int)std::min<int64_t>(2048, (int64_t)nblk(gc.N, 256));
+    R->nbf = (int)std::min<int64_t>(2048, (int64_t)nblk(gf.N, 256));
+    R->part = (double*)pb->mem.get(sizeof(double) * (3 * (size_t)(R->nbc + R->nbf) + nblk(R->nr, 256)));
     if (!R->part) return pbi_fail(PB_ENOMEM, "refined partial sums");
     if (P.precision == PB_MIXED) {
         // FP32 operator and preconditioner, rounded once from the FP64 ones
@@ -1286,61 +1303,54 @@ struct GridVecs {
     const T *d, *K;
 };
 
-// w = A v over both grids with the operator of K arrays Kc, Kf (v's derived fine values are
-// filled in first)
-template <typename T>
-void launch_apply_comp(hipStream_t s, const RefineData* R, const Grid& gc, const Grid& gf, const T* Kc, const T* Kf,
-                       T* vc, T* vf, T* wc, T* wf, const CGState* st)
+// One pass over the composite operator (v's derived fine values are filled in first); the sums of
+// OP_DOT and OP_POST go to part[0, nb) and part[3 nb, 3 nb + nblk(nr, 256))
+template <typename T, int MODE>
+void launch_apply_comp(hipStream_t s, const RefineData* R, const Grid& gc, const Grid& gf, const Split& sp, T* vc, T* vf,
+                       const OpArgs<T>& A, const CGState* st)
 {
+    const int nb = R->nbc + R->nbf;
     if (R->ng) k_fill<T><<<nblk(R->ng, 256), 256, 0, s>>>(R->ng, R->gfine, R->gpar, R->gnp, vc, vf, st);
-    k_apply<T><<<nblk(gc.N, 256), 256, 0, s>>>(gc, Kc, R->rolec, vc, wc, st);
-    k_apply<T><<<nblk(gf.N, 256), 256, 0, s>>>(gf, Kf, R->rolef, vf, wf, st);
-    if (R->nr)
-        k_restrict<T><<<nblk(R->nr, 256), 256, 0, s>>>(R->nr, R->rnode, gc, gf, R->rolef, wf, wc,
-                                                       st);
+    k_apply<T, MODE><<<nb, 256, 0, s>>>(sp, (int64_t)gc.ny * gc.S, gc.S, (int64_t)gf.ny * gf.S, gf.S, A, R->part, st);
+    if (R->nr && MODE != OP_RES)
+        k_restrict<T, MODE><<<nblk(R->nr, 256), 256, 0, s>>>(R->nr, R->rnode, gc, gf, R->rolef, A.of, A.oc, A.vc, A.rc,
+                                                             A.dc, R->part + 3 * nb, st);
 }
 
-// z = B r in the element type T: on entry z = D^-1 r; the q vectors serve as scratch; the r.z
-// partial sums go to part[0, nb).  st = null: ungated (inside a reliable update)
+// z = B r in the element type T: on entry z = w D^-1 r; the q vectors hold the residual on the way
+// and B r in the end (not at the derived nodes), so that the second smoothing step needs no pass of
+// its own; the r.z partial sums go where OP_POST puts them.  st = null: ungated (inside a reliable
+// update)
 template <typename T>
 void launch_two_level(hipStream_t s, pb_problem* pb, const Grid& gc, const Grid& gf, const Split& sp,
                       const GridVecs<T>& c, const GridVecs<T>& f, const CGState* st)
 {
     RefineData* R = pb->ref;
-    const int nb = R->nbc + R->nbf;
     T* bH = (T*)pbi_mg_rhs0(pb);
     T* eH = (T*)pbi_mg_sol0(pb);
-    k_zscale<T><<<nb, 256, 0, s>>>(sp, c.z, f.z, st);
-    launch_apply_comp<T>(s, R, gc, gf, c.K, f.K, c.z, f.z, c.q, f.q, st);
-    k_rsub<T><<<nb, 256, 0, s>>>(sp, c.r, f.r, c.q, f.q, st);
-    k_rest_h<T><<<nblk(gc.N, 256), 256, 0, s>>>(gc, gf, R->rolec, R->rolef, c.q, f.q, bH, st);
+    const OpArgs<T> A{c.K, f.K, c.z, f.z, c.q, f.q, c.r, f.r, c.d, f.d};
+    launch_apply_comp<T, OP_RES>(s, R, gc, gf, sp, c.z, f.z, A, st);
+    k_rest_h<T><<<nblk(gc.N, 256), 256, 0, s>>>(gc, gf, c.q, f.q, bH, st);
     pbi_mg_vcycle_on(pb, s, st);
-    k_prol_c<T><<<nblk(gc.N, 256), 256, 0, s>>>(gc.N, R->rolec, eH, c.z, st);
-    k_prol_f<T><<<nblk(gf.N, 256), 256, 0, s>>>(gf, gc, R->rolef, eH, f.z, st);
-    launch_apply_comp<T>(s, R, gc, gf, c.K, f.K, c.z, f.z, c.q, f.q, st);
-    k_post<T><<<nb, 256, 0, s>>>(sp, c.z, f.z, c.r, f.r, c.q, f.q, c.d, f.d, R->part, st);
+    k_prol<T><<<R->nbc + R->nbf, 256, 0, s>>>(sp, gf, gc, eH, c.z, f.z, st);
+    launch_apply_comp<T, OP_POST>(s, R, gc, gf, sp, c.z, f.z, A, st);
 }
 
-// one composite CG iteration: q = P^T K P p, alpha, x and r, z = D^-1 r (or z = B r with
+// one composite CG iteration: q = P^T K P p, alpha, x and r, z = D^-1 r (or B r, left in q, with
 // two_level, the problem whose two-level preconditioner is used), beta, p
 template <typename T>
 void launch_iteration(hipStream_t s, const RefineData* R, const Grid& gc, const Grid& gf, const Split& sp,
                       const GridVecs<T>& c, const GridVecs<T>& f, CGState* st, pb_problem* two_level = nullptr)
 {
-    const int nb = R->nbc + R->nbf;
-    if (R->ng) k_fill<T><<<nblk(R->ng, 256), 256, 0, s>>>(R->ng, R->gfine, R->gpar, R->gnp, c.p, f.p, st);
-    k_apply<T><<<nblk(gc.N, 256), 256, 0, s>>>(gc, c.K, R->rolec, c.p, c.q, st);
-    k_apply<T><<<nblk(gf.N, 256), 256, 0, s>>>(gf, f.K, R->rolef, f.p, f.q, st);
-    if (R->nr)
-        k_restrict<T><<<nblk(R->nr, 256), 256, 0, s>>>(R->nr, R->rnode, gc, gf, R->rolef, f.q, c.q,
-                                                       st);
-    k_dot<T><<<nb, 256, 0, s>>>(sp, c.p, c.q, f.p, f.q, R->part, st);
-    k_alpha<<<1, 256, 0, s>>>(R->part, nb, st);
-    k_update<T><<<nb, 256, 0, s>>>(sp, c.x, c.r, c.z, c.p, c.q, c.d, f.x, f.r, f.z, f.p, f.q, f.d, R->part, nb, st);
+    const int nb = R->nbc + R->nbf, nx = (int)nblk(R->nr, 256);
+    const OpArgs<T> A{c.K, f.K, c.p, f.p, c.q, f.q, c.r, f.r, c.d, f.d};
+    launch_apply_comp<T, OP_DOT>(s, R, gc, gf, sp, c.p, f.p, A, st);
+    k_alpha<<<1, 256, 0, s>>>(R->part, nb, nx, st);
+    k_update<T><<<nb, 256, 0, s>>>(sp, c.x, c.r, c.z, c.p, c.q, c.d, f.x, f.r, f.z, f.p, f.q, f.d,
+                                   two_level ? (T)kOmega : (T)1, R->part, nb, st);
     if (two_level) launch_two_level<T>(s, two_level, gc, gf, sp, c, f, st);
-    k_beta<<<1, 256, 0, s>>>(R->part, nb, st, 0, 0.0);
-    k_pupd<T><<<nblk(gc.N, 256), 256, 0, s>>>(gc.N, R->rolec, c.z, c.p, st);
-    k_pupd<T><<<nblk(gf.N, 256), 256, 0, s>>>(gf.N, R->rolef, f.z, f.p, st);
+    k_beta<<<1, 256, 0, s>>>(R->part, nb, two_level ? nx : 0, st, 0, 0.0);
+    k_pupd<T><<<nb, 256, 0, s>>>(sp, two_level ? c.q : c.z, two_level ? f.q : f.z, c.p, f.p, st);
 }
 
 // mixed precision: fold the FP32 correction into x, r = b - A x with the FP64 operator, and
@@ -1355,21 +1365,17 @@ void launch_reliable_update(hipStream_t s, pb_problem* pb, const Split& sp, int 
     const Grid& gf = fp->g;
     const int nb = R->nbc + R->nbf;
     k_fold<<<nb, 256, 0, s>>>(sp, pb->x, R->xc32, fp->x, R->xf32);
-    if (R->ng)
-        k_fill<double><<<nblk(R->ng, 256), 256, 0, s>>>(R->ng, R->gfine, R->gpar, R->gnp, pb->x, fp->x, nullptr);
-    k_apply<double><<<nblk(gc.N, 256), 256, 0, s>>>(gc, R->Kc, R->rolec, pb->x, R->qc, nullptr);
-    k_apply<double><<<nblk(gf.N, 256), 256, 0, s>>>(gf, R->Kf, R->rolef, fp->x, R->qf, nullptr);
-    if (R->nr)
-        k_restrict<double><<<nblk(R->nr, 256), 256, 0, s>>>(R->nr, R->rnode, gc, gf, R->rolef, R->qf,
-                                                            R->qc, nullptr);
+    const OpArgs<double> A{R->Kc, R->Kf, pb->x, fp->x, R->qc, R->qf, nullptr, nullptr, nullptr, nullptr};
+    launch_apply_comp<double, OP_RAW>(s, R, gc, gf, sp, pb->x, fp->x, A, nullptr);
     k_true_res<<<nb, 256, 0, s>>>(sp, R->bc, R->qc, R->rc, R->bf, R->qf, R->rf, R->part + 2 * nb);
-    k_replace<<<nb, 256, 0, s>>>(sp, R->rc, R->rc32, R->zc32, R->dc32, R->rf, R->rf32, R->zf32, R->df32, R->part, nb);
+    k_replace<<<nb, 256, 0, s>>>(sp, R->rc, R->rc32, R->zc32, R->dc32, R->rf, R->rf32, R->zf32, R->df32,
+                                 two_level ? (float)kOmega : 1.0f, R->part, nb);
     if (two_level) {
         const GridVecs<float> c32{R->xc32, R->rc32, R->zc32, R->pc32, R->qc32, R->dc32, R->Kc32};
         const GridVecs<float> f32{R->xf32, R->rf32, R->zf32, R->pf32, R->qf32, R->df32, R->Kf32};
         launch_two_level<float>(s, pb, gc, gf, sp, c32, f32, nullptr);
     }
-    k_ru_fin<<<1, 256, 0, s>>>(R->part, nb, pb->st, init, rtol2, delta2);
+    k_ru_fin<<<1, 256, 0, s>>>(R->part, nb, two_level ? (int)nblk(R->nr, 256) : 0, pb->st, init, rtol2, delta2);
 }
 
 }  // namespace
@@ -1390,7 +1396,7 @@ int pbi_refine_solve(pb_problem* pb, CGState* out)
     const int nb = R->nbc + R->nbf;
     CGState* st = pb->st;
     const Split sp{gc.N, gf.N, R->nbc, R->rolec, R->rolef};
-    const unsigned bc = nblk(gc.N, 256), bfn = nblk(gf.N, 256);
+    const unsigned bc = nblk(gc.N, 256);
     const GridVecs<double> c64{pb->x, R->rc, R->zc, R->pc, R->qc, R->dc, R->Kc};
     const GridVecs<double> f64{fp->x, R->rf, R->zf, R->pf, R->qf, R->df, R->Kf};
     const GridVecs<float> c32{R->xc32, R->rc32, R->zc32, R->pc32, R->qc32, R->dc32, R->Kc32};
@@ -1409,8 +1415,8 @@ int pbi_refine_solve(pb_problem* pb, CGState* out)
         RCHK(launch_fill(s, R->xc32, sizeof(float) * (size_t)gc.N));
         RCHK(launch_fill(s, R->xf32, sizeof(float) * (size_t)gf.N));
         launch_reliable_update(s, pb, sp, 1, P.rtol * P.rtol, P.inner_rtol * P.inner_rtol, two_level);
-        k_pupd<float><<<bc, 256, 0, s>>>(gc.N, R->rolec, R->zc32, R->pc32, st);
-        k_pupd<float><<<bfn, 256, 0, s>>>(gf.N, R->rolef, R->zf32, R->pf32, st);
+        k_pupd<float><<<nb, 256, 0, s>>>(sp, two_level ? R->qc32 : R->zc32, two_level ? R->qf32 : R->zf32, R->pc32,
+                                         R->pf32, st);
     } else {
         // x = 0, r = b; the first update with alpha = 0 and p = q = 0 leaves x, r and forms z
         // and the norms; p = z
@@ -1421,11 +1427,10 @@ int pbi_refine_solve(pb_problem* pb, CGState* out)
         RCHK(launch_fill(s, R->qc, sizeof(double) * (size_t)gc.N));
         RCHK(launch_fill(s, R->qf, sizeof(double) * (size_t)gf.N));
         k_update<double><<<nb, 256, 0, s>>>(sp, c64.x, c64.r, c64.z, c64.p, c64.q, c64.d, f64.x, f64.r, f64.z, f64.p,
-                                            f64.q, f64.d, R->part, nb, st);
+                                            f64.q, f64.d, two_level ? kOmega : 1.0, R->part, nb, st);
         if (two_level) launch_two_level<double>(s, pb, gc, gf, sp, c64, f64, st);
-        k_beta<<<1, 256, 0, s>>>(R->part, nb, st, 1, P.rtol * P.rtol);
-        k_pupd<double><<<bc, 256, 0, s>>>(gc.N, R->rolec, R->zc, R->pc, st);
-        k_pupd<double><<<bfn, 256, 0, s>>>(gf.N, R->rolef, R->zf, R->pf, st);
+        k_beta<<<1, 256, 0, s>>>(R->part, nb, two_level ? (int)nblk(R->nr, 256) : 0, st, 1, P.rtol * P.rtol);
+        k_pupd<double><<<nb, 256, 0, s>>>(sp, two_level ? R->qc : R->zc, two_level ? R->qf : R->zf, R->pc, R->pf, st);
     }
     RCHK(hipGetLastError());
     const int M = 16;
@@ -1451,8 +1456,8 @@ int pbi_refine_solve(pb_problem* pb, CGState* out)
             breakdown = h.status == 2;
             launch_reliable_update(s, pb, sp, 0, 0.0, 0.0, two_level);
             if (!breakdown && launched < P.max_iter) {
-                k_pupd<float><<<bc, 256, 0, s>>>(gc.N, R->rolec, R->zc32, R->pc32, st);
-                k_pupd<float><<<bfn, 256, 0, s>>>(gf.N, R->rolef, R->zf32, R->pf32, st);
+                k_pupd<float><<<nb, 256, 0, s>>>(sp, two_level ? R->qc32 : R->zc32, two_level ? R->qf32 : R->zf32, R->pc32,
+                                         R->pf32, st);
             }
             RCHK(hipGetLastError());
             RCHK(hipMemcpyAsync(&h, st, sizeof(CGState), hipMemcpyDeviceToHost, s));
