@@ -871,8 +871,7 @@ int pbi_build_continue(pb_problem* pb)
     // solver scalars and partial sums
     pb->nb = pb->ts.items;
     pb->nbres = residual_blocks(g);
-    if (prm->precond == PB_PRECOND_JACOBI && prm->tile_planes == 0)
-        pb->small = small_shape(g, prm->precision == PB_MIXED ? (int)sizeof(float) : (int)sizeof(double));
+    if (prm->precond == PB_PRECOND_JACOBI && prm->tile_planes == 0) pb->small = small_shape(g);
     pb->part = dalloc<double>(pb, 5 * (size_t)std::max(pb->nb, 2 * pb->small.items), &rc);
     CK(rc);
     pb->part_res = dalloc<double>(pb, 3 * (size_t)pb->nbres, &rc);

@@ -46,6 +46,21 @@ struct Grid {
     }
 };
 
+// The tile of block b of nb: blocks go to the 8 XCDs round-robin (b % 8), and runs of RUN consecutive
+// tiles go to the XCDs in turn, so that a run's neighbouring tiles share one L2 and expensive regions
+// of the grid are spread over all XCDs; of the tiles that fill no round of runs each XCD gets one range.
+template <int RUN>
+__device__ __forceinline__ int xcd_tile(int b, int nb)
+{
+    const int xcd = b & 7, full = nb / (8 * RUN) * (8 * RUN);
+    if (b < full) {
+        const int t = b >> 3;
+        return ((t / RUN) * 8 + xcd) * RUN + t % RUN;
+    }
+    const int q8 = (nb - full) >> 3, rem = nb & 7;
+    return full + xcd * q8 + (xcd < rem ? xcd : rem) + ((b - full) >> 3);
+}
+
 struct Bins {          // atom cell list: bins of edge bs covering the atom centres
     double lox, loy, loz, bs;
     int nbx, nby, nbz;
@@ -248,7 +263,7 @@ struct SmallShape {
     int nkt = 0, njt = 0, items = 0;   // tiles along z and y, all tiles (0: not used)
     int per = 0;                       // nodes per thread
 };
-SmallShape small_shape(const Grid& g, int elem);   // elem: bytes of the iteration's numbers
+SmallShape small_shape(const Grid& g);
 template <typename T>
 hipError_t launch_cg_small(hipStream_t s, const Grid& g, const SmallShape& ss, const CGBufs<T>& B, Coef c, int t);
 hipError_t launch_stream_copy(hipStream_t s, const void* a, void* b, size_t bytes);

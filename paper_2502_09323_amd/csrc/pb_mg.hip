@@ -267,29 +267,17 @@ inline RB rb_tiled(const Grid& g)
     return r;
 }
 
-// Block `local` of a level-0 pass of nb blocks takes tile item(local): blocks are dealt to the 8 XCDs
-// round-robin (a problem's blocks start at a multiple of 8), and runs of kRun consecutive tiles (along
-// z fastest, then rows, then plane slabs) go to the XCDs in turn; of the tiles that fill no
-// round of runs each XCD gets one range.  Within a run the neighbour rows that a tile reads were mostly brought into
-// that XCD's L2 by the tiles just before it; the turns spread the slabs that cross the solute's
-// surface, whose tiles take about twice the time, over all XCDs.  With one eighth of the tiles per XCD
-// the middle slabs' XCDs ended last: half-sweep at 385^3 137 -> 116 us, operator pass 327 -> 291, the
-// whole call 72.4 -> 68.6 ms, 257^3 22.8 -> 22.2.  Runs of 16, 32, 64, 128 and 256 tiles: 385^3 68.3,
-// 68.6, 68.6, 68.6, 69.1 ms; 257^3 22.7, 22.6, 22.2, 22.2, 22.2; 129^3 4.64, 4.60, 4.58, 4.62, 4.72.
+// Runs of kRun tiles (along z fastest, then rows, then plane slabs) per XCD: the slabs that cross the
+// solute's surface, whose tiles take about twice the time, spread over all XCDs.  With one eighth of
+// the tiles per XCD the middle slabs' XCDs ended last: half-sweep at 385^3 137 -> 116 us, operator pass
+// 327 -> 291, the whole call 72.4 -> 68.6 ms, 257^3 22.8 -> 22.2.  Runs of 16, 32, 64, 128 and 256
+// tiles: 385^3 68.3, 68.6, 68.6, 68.6, 69.1 ms; 257^3 22.7, 22.6, 22.2, 22.2, 22.2; 129^3 4.64, 4.60,
+// 4.58, 4.62, 4.72.
 constexpr int kRun = 64;
 
 __device__ __forceinline__ VB vb_rb(const RB& r, int local, int nb)
 {
-    const int xcd = local & 7, full = nb / (8 * kRun) * (8 * kRun);
-    int item;
-    if (local < full) {
-        const int t = local >> 3;
-        item = ((t / kRun) * 8 + xcd) * kRun + t % kRun;
-    } else {
-        const int q8 = (nb - full) >> 3, rem = nb & 7;
-        item = full + xcd * q8 + (xcd < rem ? xcd : rem) + ((local - full) >> 3);
-    }
-    return vb_of(item, rb_gx(r), rb_gy(r));
+    return vb_of(xcd_tile<kRun>(local, nb), rb_gx(r), rb_gy(r));
 }
 
 // blocks along z of a coarse-level pass over all interior nodes or over the nodes of one colour

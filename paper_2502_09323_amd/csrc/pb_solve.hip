@@ -22,8 +22,8 @@
 // The iteration kernel tiles the interior into columns of ZW (z) x TY (y) nodes and marches
 // along x over a chunk of planes, carrying the x-neighbours in registers and staging the
 // current plane with its y/z halo in LDS.  Tiles are numbered z-fastest and handed out so
-// that each XCD gets one contiguous range of tiles, which keeps the halo rows of
-// neighbouring tiles in the same L2.
+// that each XCD gets runs of consecutive tiles, which keeps the halo rows of neighbouring
+// tiles in the same L2.
 #include "pb_internal.h"
 #include "pb_stencil.h"
 
@@ -110,10 +110,11 @@ __device__ __forceinline__ void iter_body(const Grid& g, const TileShape& ts, co
     const T aT = (T)st->alpha, bT = (T)st->beta;
     const T kin = (T)cf.kin, kout = (T)cf.kout, mass = (T)cf.mass;
 
-    // XCD-aware bijective block -> tile map (blocks are dealt round-robin to 8 XCDs)
-    const int W = ts.items, b = bid;
-    const int q8 = W >> 3, rem = W & 7, xcd = b & 7;
-    const int item = xcd * q8 + (xcd < rem ? xcd : rem) + (b >> 3);
+    // Runs of 16 tiles per XCD (with an eighth of the grid per XCD the XCDs of the surface's tiles,
+    // whose table reads differ by lane, ended last): 385^3 mixed, per iteration, runs of 1, 2, 4, 8,
+    // 16, 64 and 256 tiles 616, 519, 505, 504, 502, 515, 528 us, eighths 527; 257^3 FP64 251, 249,
+    // 248, 246.5, 246.3, eighths 253.
+    const int item = xcd_tile<16>(bid, ts.items);
     const int kt = item % ts.nkt;
     const int t2 = item / ts.nkt;
     const int jt = t2 % ts.njt;
@@ -398,8 +399,8 @@ __global__ void __launch_bounds__(256) k_cg_tail(const double* __restrict__ part
 // block of it changes but for chunk0, and the chunk's last iteration is closed by k_cg_tail.  Same
 // recurrences as iter_body; the sums in another order.
 // Per iteration in us (FP64 | mixed, before -> now): 33^3 14.8 -> 6.9 | 14.2 -> 7.8, 65^3 15.0 ->
-// 8.5 | 13.9 -> 8.5, 97^3 25.3 -> 17.8 | 17.6 -> 13.9, 129^3 44.9 -> 34.6 | 30.1 -> 25.7, 145^3
-// 65.3 -> 52.3 | 43.5 -> 39.0.  At 65^3 what is left is launch, one round of loads, two block
+// 8.5 | 13.9 -> 8.0, 97^3 25.3 -> 17.7 | 17.6 -> 13.9, 129^3 44.9 -> 34.3 | 30.1 -> 25.5, 145^3
+// 65.3 -> 52.1 | 43.5 -> 39.1.  At 65^3 what is left is launch, one round of loads, two block
 // reductions and the store; from 113^3 on it is cache bandwidth.
 constexpr int SM_Y = 4, SM_T = 512;
 
@@ -456,9 +457,9 @@ __global__ void __launch_bounds__(SM_T) k_cg_small(Grid g, SmallShape ss, CGBufs
     const int it = t0 == 0 ? st->iter_count : st->chunk0 + t0;
     const int nw = it & 1, od = nw ^ 1, tid = (int)threadIdx.x;
     const T kin = (T)cf.kin, kout = (T)cf.kout, mass = (T)cf.mass;
-    // contiguous ranges of tiles per XCD, as in iter_body
-    const int q8 = ss.items >> 3, rem = ss.items & 7, xcd = (int)blockIdx.x & 7;
-    const int item = xcd * q8 + (xcd < rem ? xcd : rem) + ((int)blockIdx.x >> 3);
+    // one eighth of the tiles per XCD (no tile costs more than another here; runs of 4, 16 and 64 tiles:
+    // 97^3 FP64 18.9, 18.0, 17.8 us, eighths 17.8)
+    const int item = xcd_tile<1 << 24>((int)blockIdx.x, ss.items);
     const int kt = item % ss.nkt, t2 = item / ss.nkt, jt = t2 % ss.njt, xt = t2 / ss.njt;
     const int k0 = 1 + kt * 32, j0 = 1 + jt * SM_Y, i0 = 1 + xt * SM_X;
     const int kl = tid & 31, jl = (tid >> 5) & 3, il = tid >> 7;
@@ -961,20 +962,20 @@ hipError_t launch_cg_iter(hipStream_t s, const Grid& g, const TileShape& ts, con
     return hipGetLastError();
 }
 
-// One launch per iteration while the iteration's vectors (z, w, p twice, x) and codes stay in the
-// last-level cache (256 MB) with what else lives there: at 161^3 in FP64 (250 MB) both forms take
-// 78 us, at 193^3 131 (marching) against 158, as the halos of the small tiles then come from memory;
-// in FP32 145^3 (98 MB) 39.0 against 43.5 and 177^3 (177 MB) 66 against 68.
-constexpr int64_t kSmallBytes = (int64_t)200 << 20;
+// One launch per iteration while the grid's vectors (z, w, p twice, x) mostly stay in the last-level
+// cache; above, the small tiles' halos come from memory.  us per iteration, marching against this:
+// FP64 97^3 24.7, 17.7; 145^3 63.1, 52.1; 153^3 66.7, 63.3; 161^3 68.1, 79.9; 193^3 112, 158.  FP32
+// 97^3 19.5, 13.9; 145^3 42.3, 39.1; 153^3 44.7, 44.5; 161^3 46.3, 45.9; 177^3 62.7, 66.7.
+constexpr int64_t kSmallNodes = 3700000;
 
 // Nodes per thread: one while a block per CU covers the grid (33^3: 6.9 us, with two 7.6; 49^3, more
 // blocks than that, 8.2 and 7.9), two while all blocks of that size run at once (three per CU; 81^3
 // 14.3 us, with four 15.6), and four above, where halo traffic counts (97^3: 17.6, with two 19.0;
 // 129^3: 34.4 and 37.9).
-SmallShape small_shape(const Grid& g, int elem)
+SmallShape small_shape(const Grid& g)
 {
     SmallShape t;
-    if (g.N * (7 * elem + 4) > kSmallBytes) return t;
+    if ((int64_t)g.nx * g.ny * g.nz > kSmallNodes) return t;
     t.nkt = (g.nz - 2 + 31) / 32;
     t.njt = (g.ny - 2 + SM_Y - 1) / SM_Y;
     auto tiles = [&](int n) { return t.nkt * t.njt * ((g.nx - 2 + 4 * n - 1) / (4 * n)); };
