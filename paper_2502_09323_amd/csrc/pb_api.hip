@@ -865,7 +865,7 @@ int pbi_build_continue(pb_problem* pb)
     } else if (prm->bc == PB_BC_USER) {
         HIPCHK(launch_bc_user(s, g, T.full, pb->gb));
     }
-    HIPCHK(launch_diag_lift(s, g, pb->code, pb->ck64, pb->cf, pb->gb, pb->rhs, nullptr, nullptr));
+    HIPCHK(launch_lift(s, g, pb->code, pb->ck64, pb->cf, pb->gb, pb->rhs));
     HIPCHK(launch_mc_weights(s, g, pb->code, pb->cutbase, pb->ncut, pb->cutkey, pb->rp, pb->wp));
 
     // solver scalars and partial sums

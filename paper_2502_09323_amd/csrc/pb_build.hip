@@ -25,10 +25,12 @@ constexpr double kPi = 3.14159265358979323846;
 
 __device__ __forceinline__ void decode(const Grid& g, int64_t e, int& i, int& j, int& k)
 {
-    int64_t row = e / g.S;
-    k = (int)(e - row * g.S) - Z0;
-    j = (int)(row % g.ny);
-    i = (int)(row / g.ny);
+    // 32-bit divisions: a grid holds at most 2^29 elements (64-bit ones were most of the per-node
+    // kernels' instructions)
+    const uint32_t u = (uint32_t)e, row = u / (uint32_t)g.S, r2 = row / (uint32_t)g.ny;
+    k = (int)(u - row * (uint32_t)g.S) - Z0;
+    j = (int)(row - r2 * (uint32_t)g.ny);
+    i = (int)r2;
 }
 
 __device__ __forceinline__ bool is_box(const Grid& g, int i, int j, int k)
@@ -110,46 +112,70 @@ __global__ void k_bin_sort(int nbins, const int* start, int* ids)
     }
 }
 
-// single-block exclusive scan of n ints into out[0..n] (out[n] = total; out may be in), in
-// tiles of 4096: each thread takes four consecutive elements, the 1024 partial sums of a tile
-// are scanned with wave shuffles and a pass over the 16 wave totals, and the running total
-// carries from tile to tile.  Each element is read before it is written, by the same thread,
-// so in == out is safe.
-__global__ void __launch_bounds__(1024) k_scan1(const int* in, int n, int* out)
+// exclusive scan of n ints into out[0..n] (out[n] = total; out may be in) by one block, block b taking
+// the b-th array, in tiles of 4096: each thread takes four consecutive elements, the 1024 partial sums
+// of a tile are scanned with wave shuffles and a pass over the 16 wave totals, and the running total
+// carries from tile to tile.  A tile is loaded while the one before is scanned.  Each element is read
+// before it is written, by the same thread, so in == out is safe.  A chain of barriers and shuffles on
+// one compute unit, with the two arrays of launch_scan2 side by side: 241 k counts each of 385^3
+// 272 us (one after the other, four barriers' worth per tile) -> 70 (sixteen elements per thread: 211, as a wave's loads then span 64 lines each).
+struct ScanArgs {
+    const int* in[2];
+    int* out[2];
+};
+
+__global__ void __launch_bounds__(1024) k_scan(ScanArgs A, int n, int* totals)
 {
-    __shared__ int wtot[16];
+    __shared__ int wtot[2][16];
+    const int* in = blockIdx.x ? A.in[1] : A.in[0];
+    int* out = blockIdx.x ? A.out[1] : A.out[0];
     const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
-    int carry = 0;
-    for (int base = 0; base < n; base += 4096) {
+    const bool wide = (((uintptr_t)in | (uintptr_t)out) & 15) == 0;   // 16-byte accesses allowed
+    auto load = [&](int e0) {
+        int4 v{0, 0, 0, 0};
+        if (wide && e0 + 3 < n) return *reinterpret_cast<const int4*>(in + e0);
+        if (e0 < n) v.x = in[e0];
+        if (e0 + 1 < n) v.y = in[e0 + 1];
+        if (e0 + 2 < n) v.z = in[e0 + 2];
+        if (e0 + 3 < n) v.w = in[e0 + 3];
+        return v;
+    };
+    int carry = 0, par = 0;
+    int4 nx = load(4 * (int)threadIdx.x);
+    for (int base = 0; base < n; base += 4096, par ^= 1) {
         const int e0 = base + 4 * (int)threadIdx.x;
-        int v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = e0 + u < n ? in[e0 + u] : 0;
-        const int s = (v[0] + v[1]) + (v[2] + v[3]);
+        const int4 v = nx;
+        nx = load(e0 + 4096);
+        const int s = (v.x + v.y) + (v.z + v.w);
         int incl = s;
         for (int off = 1; off < 64; off <<= 1) {
             const int t = __shfl_up(incl, off, 64);
             if (lane >= off) incl += t;
         }
-        if (lane == 63) wtot[w] = incl;
+        if (lane == 63) wtot[par][w] = incl;
         __syncthreads();
         int before = 0, total = 0;
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-            const int t = wtot[q];
+            const int t = wtot[par][q];
             before += q < w ? t : 0;
             total += t;
         }
-        int run = carry + before + incl - s;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (e0 + u < n) out[e0 + u] = run;
-            run += v[u];
+        const int r0 = carry + before + incl - s, r1 = r0 + v.x, r2 = r1 + v.y, r3 = r2 + v.z;
+        if (wide && e0 + 3 < n) {
+            *reinterpret_cast<int4*>(out + e0) = int4{r0, r1, r2, r3};
+        } else {
+            if (e0 < n) out[e0] = r0;
+            if (e0 + 1 < n) out[e0 + 1] = r1;
+            if (e0 + 2 < n) out[e0 + 2] = r2;
+            if (e0 + 3 < n) out[e0 + 3] = r3;
         }
         carry += total;
-        __syncthreads();
     }
-    if (threadIdx.x == 0) out[n] = carry;
+    if (threadIdx.x == 0) {
+        out[n] = carry;
+        if (totals) totals[blockIdx.x] = carry;
+    }
 }
 
 // ---- classification -------------------------------------------------------------------
@@ -908,41 +934,36 @@ __global__ void __launch_bounds__(256) k_bc_user(Grid g, const double* full, dou
     gb[g.idx(i, j, k)] = full[((int64_t)i * g.ny + j) * g.nz + k];
 }
 
-// ---- diagonal, Jacobi inverse, boundary lift ------------------------------------------------
+// ---- boundary lift --------------------------------------------------------------------------
 
 __device__ __forceinline__ double edgeK(uint32_t c, int ax, const double* ck, const Coef& cf)
 {
     return stencil::edgeK(c, ax, ck, cf.kin, cf.kout);
 }
 
-__global__ void __launch_bounds__(256) k_diag_lift(Grid g, const uint32_t* code, const double* ck,
-                                                   Coef cf, const double* gb, double* rhs,
-                                                   float* dinv, double* diag)
+// Only the nodes next to the box do more than read seven codes (with the whole row of the operator
+// formed at every node 651 us at 385^3, so 272).
+__global__ void __launch_bounds__(256) k_lift(Grid g, const uint32_t* __restrict__ code, const double* __restrict__ ck,
+                                              Coef cf, const double* __restrict__ gb, double* __restrict__ rhs)
 {
     int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= g.N) return;
-    uint32_t c = code[e];
-    if (c & C_BOX) {
-        if (dinv) dinv[e] = 0.0f;
-        if (diag) diag[e] = 0.0;
-        return;
-    }
+    const uint32_t c = code[e];
+    if (c & C_BOX) return;
     const int64_t sx = (int64_t)g.ny * g.S, sy = g.S;
     const int64_t nb[6] = {e - sx, e + sx, e - sy, e + sy, e - 1, e + 1};
-    double K[6];
-    K[0] = edgeK(code[e - sx], 0, ck, cf);
-    K[1] = edgeK(c, 0, ck, cf);
-    K[2] = edgeK(code[e - sy], 1, ck, cf);
-    K[3] = edgeK(c, 1, ck, cf);
-    K[4] = edgeK(code[e - 1], 2, ck, cf);
-    K[5] = edgeK(c, 2, ck, cf);
-    const double D = stencil::diag_sum(K[0], K[1], K[2], K[3], K[4], K[5], (c & C_SOLUTE) ? 0.0 : cf.mass);
+    uint32_t cn[6], any = 0;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        cn[q] = code[nb[q]];
+        any |= cn[q];
+    }
+    if (!(any & C_BOX)) return;
     double lift = 0.0;
+#pragma unroll
     for (int q = 0; q < 6; ++q)
-        if (code[nb[q]] & C_BOX) lift += K[q] * gb[nb[q]];
+        if (cn[q] & C_BOX) lift += edgeK((q & 1) ? c : cn[q], q >> 1, ck, cf) * gb[nb[q]];
     rhs[e] += lift;
-    if (dinv) dinv[e] = (float)(1.0 / D);
-    if (diag) diag[e] = D;
 }
 
 // ---- marching-cubes area weights ------------------------------------------------------------
@@ -1161,7 +1182,7 @@ hipError_t launch_bins(hipStream_t s, const Atoms& at, Bins& b, int* cnt, int* s
     hipError_t err = launch_fill(s, cnt, sizeof(int) * (size_t)nb);
     if (err != hipSuccess) return err;
     k_bin_count<<<nblk(at.n, 256), 256, 0, s>>>(at, b, cnt);
-    k_scan1<<<1, 1024, 0, s>>>(cnt, nb, start);
+    k_scan<<<1, 1024, 0, s>>>(ScanArgs{{cnt, nullptr}, {start, nullptr}}, nb, nullptr);
     err = hipMemcpyAsync(cursor, start, sizeof(int) * (size_t)nb, hipMemcpyDeviceToDevice, s);
     if (err != hipSuccess) return err;
     k_bin_scatter<<<nblk(at.n, 256), 256, 0, s>>>(at, b, cursor, ids);
@@ -1187,20 +1208,13 @@ hipError_t launch_cutflags(hipStream_t s, const Grid& g, uint32_t* cls, int* blk
 
 hipError_t launch_scan1(hipStream_t s, const int* in, int n, int* out)
 {
-    k_scan1<<<1, 1024, 0, s>>>(in, n, out);
+    k_scan<<<1, 1024, 0, s>>>(ScanArgs{{in, nullptr}, {out, nullptr}}, n, nullptr);
     return hipGetLastError();
 }
 
 hipError_t launch_scan2(hipStream_t s, int* a, int* b, int n, int* totals)
 {
-    // in-place exclusive scans through a copy: out[i] written after in[i] is read by the
-    // same thread and only the carry crosses chunks, so in == out is safe
-    k_scan1<<<1, 1024, 0, s>>>(a, n, a);
-    k_scan1<<<1, 1024, 0, s>>>(b, n, b);
-    hipError_t err = hipMemcpyAsync(totals, a + n, sizeof(int), hipMemcpyDeviceToDevice, s);
-    if (err != hipSuccess) return err;
-    err = hipMemcpyAsync(totals + 1, b + n, sizeof(int), hipMemcpyDeviceToDevice, s);
-    if (err != hipSuccess) return err;
+    k_scan<<<2, 1024, 0, s>>>(ScanArgs{{a, b}, {a, b}}, n, totals);
     return hipGetLastError();
 }
 
@@ -1395,10 +1409,10 @@ hipError_t launch_bc_user(hipStream_t s, const Grid& g, const double* full, doub
     return hipGetLastError();
 }
 
-hipError_t launch_diag_lift(hipStream_t s, const Grid& g, const uint32_t* code, const double* ck64,
-                            Coef c, const double* gb, double* rhs, float* dinv, double* diag)
+hipError_t launch_lift(hipStream_t s, const Grid& g, const uint32_t* code, const double* ck64, Coef c,
+                       const double* gb, double* rhs)
 {
-    k_diag_lift<<<nblk(g.N, 256), 256, 0, s>>>(g, code, ck64, c, gb, rhs, dinv, diag);
+    k_lift<<<nblk(g.N, 256), 256, 0, s>>>(g, code, ck64, c, gb, rhs);
     return hipGetLastError();
 }
 

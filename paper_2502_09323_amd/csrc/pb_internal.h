@@ -222,8 +222,9 @@ bool dh_interp_plan(const Grid& g, const Atoms& at, const double* lo, const doub
 hipError_t launch_bc_dh_interp(hipStream_t s, const Grid& g, const Atoms& at, double kD, double eps_out,
                                const DhInterp& d, double* part, double* gb);
 hipError_t launch_bc_user(hipStream_t s, const Grid& g, const double* full, double* gb);
-hipError_t launch_diag_lift(hipStream_t s, const Grid& g, const uint32_t* code, const double* ck64,
-                            Coef c, const double* gb, double* rhs, float* dinv, double* diag);
+// b += K g over the edges to box nodes
+hipError_t launch_lift(hipStream_t s, const Grid& g, const uint32_t* code, const double* ck64, Coef c,
+                       const double* gb, double* rhs);
 hipError_t launch_mc_weights(hipStream_t s, const Grid& g, const uint32_t* code, const int* cutbase,
                              int64_t ncut, const int64_t* cutkey, const double* rp, double* wp);
 hipError_t launch_fill(hipStream_t s, void* p, size_t bytes);
