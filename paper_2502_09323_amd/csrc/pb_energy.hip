@@ -10,9 +10,10 @@
 //   E_pol = 1/2 lB sum q_i phi_pol(i),  E_ion = 1/2 lB sum q_i phi_ion(i),
 //   E_coul = 1/2 lB sum_i q_i sum_{j != i} q_j /(eps_in r_ij)
 //
-// The atoms x cut-points sum is the FP64 vector-ALU hot spot: points are staged through
-// LDS in tiles, each thread owns a few atoms, and the cut list is split into chunks whose
-// per-atom partials are summed in chunk order, so the result does not depend on timing.
+// The direct atoms x cut-points sum is FP64 vector-ALU bound: points are staged through LDS in
+// tiles, each thread owns a few atoms, and the cut list is split into chunks whose per-atom
+// partials are summed in chunk order, so the result does not depend on timing.  Large problems
+// take the box expansions of pb_tree.hip instead, which leave partials of the same form.
 #include "pb_internal.h"
 
 #include <algorithm>
