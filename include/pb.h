@@ -329,7 +329,8 @@ int pb_get_profile(const pb_problem* pb, double* stencil_ms_avg, double* update_
 
 /* With profiling on in the problem's context: HIP-event time (ms) of the energy N-body
  * kernel (atoms x cut points, FP64; a12) of the last pb_energy, and its number of pairs
- * (n_atoms * n_cut); both 0 when it was not timed. */
+ * (n_atoms * n_cut); both 0 when it was not timed.
+ * A read-back by box expansions (many atoms x cut points) does not run that kernel: both 0. */
 int pb_get_energy_profile(const pb_problem* pb, double* nbody_ms, double* pairs);
 
 /* Attainable-bandwidth reference: `reps` launches of a plain streaming copy of `bytes`
