@@ -303,13 +303,11 @@ int pbi_mixed_begin(pb_problem* pb)
     hipStream_t s = pb->ctx->stream;
     const size_t N = (size_t)pb->g.N;
     const pb_params& P = pb->prm;
-    HIPCHK(launch_fill(s, pb->x, sizeof(double) * N));
-    HIPCHK(launch_fill(s, pb->d32, sizeof(float) * N));
-    for (int k = 0; k < 2; ++k) {
-        HIPCHK(launch_fill(s, pb->z32[k], sizeof(float) * N));
-        HIPCHK(launch_fill(s, pb->w32[k], sizeof(float) * N));
-        HIPCHK(launch_fill(s, pb->p32[k], sizeof(float) * N));
-    }
+    FillList fl;
+    fl.add(pb->x, sizeof(double) * N).add(pb->d32, sizeof(float) * N);
+    for (int k = 0; k < 2; ++k)
+        fl.add(pb->z32[k], sizeof(float) * N).add(pb->w32[k], sizeof(float) * N).add(pb->p32[k], sizeof(float) * N);
+    HIPCHK(launch_fill(s, fl));
     // first "update": z32 = D^-1 (b - A*0), the norms and the mixed iteration state
     HIPCHK(launch_ru_begin(s, pb->st));
     HIPCHK(launch_ru_residual(s, pb->g, pb->code, pb->ck64, pb->ck32, pb->cf, pb->rhs, pb->x, pb->z32, pb->part_res,
@@ -821,8 +819,7 @@ int pbi_build_continue(pb_problem* pb)
     CK(rc);
     pb->ck32 = dalloc<float>(pb, 3 * ns1, &rc);
     CK(rc);
-    HIPCHK(launch_fill(s, pb->ck64, sizeof(double) * 3 * ns1));
-    HIPCHK(launch_fill(s, pb->ck32, sizeof(float) * 3 * ns1));
+    HIPCHK(launch_fill(s, FillList{}.add(pb->ck64, sizeof(double) * 3 * ns1).add(pb->ck32, sizeof(float) * 3 * ns1)));
     pb->alpha = dalloc<double>(pb, nc1, &rc);
     CK(rc);
     pb->kcut = dalloc<double>(pb, nc1, &rc);
@@ -848,8 +845,7 @@ int pbi_build_continue(pb_problem* pb)
     T.acell = dalloc<double>(pb, 8 * (size_t)std::max<int64_t>(pb->na, 1), &rc);
     CK(rc);
     HIPCHK(launch_deposit(s, g, T.bn, at, T.acell, pb->rhs));
-    HIPCHK(launch_fill(s, pb->gb, sizeof(double) * N));
-    HIPCHK(launch_fill(s, pb->x, sizeof(double) * N));
+    HIPCHK(launch_fill(s, FillList{}.add(pb->gb, sizeof(double) * N).add(pb->x, sizeof(double) * N)));
     if (prm->bc == PB_BC_DH && pb->na > 0) {
         DhInterp in;
         const bool interp = prm->precision == PB_MIXED && dh_interp_plan(g, at, pb->alo, pb->ahi, pb->kD, &in);

@@ -227,6 +227,22 @@ hipError_t launch_lift(hipStream_t s, const Grid& g, const uint32_t* code, const
                        const double* gb, double* rhs);
 hipError_t launch_mc_weights(hipStream_t s, const Grid& g, const uint32_t* code, const int* cutbase,
                              int64_t ncut, const int64_t* cutkey, const double* rp, double* wp);
+// Zero fill of up to kMax buffers (16-byte aligned) by one launch, a kernel (no memset nodes, so callers
+// may capture it in a graph).
+struct FillList {
+    static constexpr int kMax = 24;
+    int n = 0;
+    void* p[kMax];
+    int64_t bytes[kMax];
+    int first[kMax + 1];   // first block of each buffer
+    FillList& add(void* q, size_t b)
+    {
+        p[n] = q;
+        bytes[n++] = (int64_t)b;
+        return *this;
+    }
+};
+hipError_t launch_fill(hipStream_t s, FillList l);
 hipError_t launch_fill(hipStream_t s, void* p, size_t bytes);
 hipError_t launch_export_coeffs(hipStream_t s, const Grid& g, const uint32_t* code, const double* ck64, Coef c,
                                 const double* rhs, uint8_t* sol, double* kx, double* ky, double* kz,

@@ -2183,13 +2183,30 @@ int setup_levels(pb_problem* pb, MGData* G, hipStream_t s)
     G->sub_lds = G->ls < G->nlev && G->g[G->ls].nx < 2048 && G->g[G->ls].ny < 1024 && G->g[G->ls].nz < 1024 &&
                  colour_threads(G->g[G->ls]) <= (int64_t)kSubOwn<T> * kSubThreads &&
                  sub_lds_bytes(sizeof(T), G->g, G->ls, G->nlev) <= kSubLdsBytes;
+    // the levels' arrays, all zeroed by one launch: FP64 coefficients, and in the element type K
+    // (three), diagonal, 1/diagonal, the level's residual, iterate and right-hand side
+    static_assert(2 * (PB_MG_MAX_LEVELS - 1) + 1 <= FillList::kMax, "fill list");
+    const RB rb = rb_tiled(pb->g);
+    FillList fl;
+    double* c64s[PB_MG_MAX_LEVELS] = {};
+    T* vs[PB_MG_MAX_LEVELS] = {};
+    for (int l = 1; l < G->nlev; ++l) {
+        const size_t N = (size_t)G->g[l].N;
+        c64s[l] = (double*)pb->mem.get(sizeof(double) * 4 * N);
+        vs[l] = (T*)pb->mem.get(sizeof(T) * 8 * N);
+        if (!c64s[l] || !vs[l]) return pbi_fail(PB_ENOMEM, "multigrid levels");
+        fl.add(c64s[l], sizeof(double) * 4 * N).add(vs[l], sizeof(T) * 8 * N);
+    }
+    G->code_rb = (uint32_t*)pb->mem.get(sizeof(uint32_t) * (size_t)rb.N);
+    if (!G->code_rb) return pbi_fail(PB_ENOMEM, "multigrid codes");
+    T* v0 = (T*)pb->mem.get(sizeof(T) * 8 * (size_t)rb.N);
+    if (!v0) return pbi_fail(PB_ENOMEM, "multigrid level-0 vectors");
+    RCHK(launch_fill(s, fl.add(v0, sizeof(T) * 8 * (size_t)rb.N)));
     // FP64 coefficients of every coarse level, then the element-type copies
     const double *pkx = nullptr, *pky = nullptr, *pkz = nullptr, *pm = nullptr;
     for (int l = 1; l < G->nlev; ++l) {
         const Grid& gc = G->g[l];
-        double* c64 = (double*)pb->mem.get(sizeof(double) * 4 * (size_t)gc.N);
-        if (!c64) return pbi_fail(PB_ENOMEM, "multigrid levels");
-        RCHK(launch_fill(s, c64, sizeof(double) * 4 * (size_t)gc.N));
+        double* c64 = c64s[l];
         double *kx = c64, *ky = c64 + gc.N, *kz = c64 + 2 * gc.N, *m = c64 + 3 * gc.N;
         FineSrc F;
         F.g = G->g[l - 1];
@@ -2204,10 +2221,7 @@ int setup_levels(pb_problem* pb, MGData* G, hipStream_t s)
         F.m = pm;
         const int64_t nn = (int64_t)gc.nx * gc.ny * gc.nz;
         k_coarsen<<<nblk(nn, 256), 256, 0, s>>>(F, gc, kx, ky, kz, m);
-        // K (three), diagonal, 1/diagonal, and the level's residual, iterate and right-hand side
-        T* v = (T*)pb->mem.get(sizeof(T) * 8 * (size_t)gc.N);
-        if (!v) return pbi_fail(PB_ENOMEM, "multigrid levels");
-        RCHK(launch_fill(s, v, sizeof(T) * 8 * (size_t)gc.N));
+        T* v = vs[l];
         for (int d = 0; d < 3; ++d) G->K[l][d] = v + d * gc.N;
         G->diag[l] = v + 3 * gc.N;
         G->dinv[l] = v + 4 * gc.N;
@@ -2225,15 +2239,9 @@ int setup_levels(pb_problem* pb, MGData* G, hipStream_t s)
     // level 0 in the red-black layout: the codes, 1 / diagonal, the red residual and the CG
     // vectors r, z, p (two), q and the correction x (x and b of level 0 are z and r)
     const Grid& g0 = pb->g;
-    const RB rb = rb_tiled(g0);
     G->Sh = rb.Sh;
     G->Nrb = rb.N;
-    G->code_rb = (uint32_t*)pb->mem.get(sizeof(uint32_t) * (size_t)rb.N);
-    if (!G->code_rb) return pbi_fail(PB_ENOMEM, "multigrid codes");
     k_rb_code<<<(unsigned)std::min<int64_t>(65536, nblk(rb.N, 256)), 256, 0, s>>>(g0, rb, pb->code, G->code_rb);
-    T* v0 = (T*)pb->mem.get(sizeof(T) * 8 * (size_t)rb.N);
-    if (!v0) return pbi_fail(PB_ENOMEM, "multigrid level-0 vectors");
-    RCHK(launch_fill(s, v0, sizeof(T) * 8 * (size_t)rb.N));
     void** dst[8] = {&G->dinv[0], &G->r[0], &G->cr, &G->cz, &G->cp, &G->cp2, &G->cq, &G->cx};
     for (int v = 0; v < 8; ++v) *dst[v] = v0 + v * rb.N;
     G->nb = rb_blocks(rb);
@@ -2300,11 +2308,12 @@ template <typename T>
 int start_t(pb_problem* pb, hipStream_t s)
 {
     MGData* G = pb->mg;
-    RCHK(launch_fill(s, pb->x, sizeof(double) * (size_t)pb->g.N));
-    RCHK(launch_fill(s, G->cx, sizeof(T) * (size_t)G->Nrb));
-    RCHK(launch_fill(s, G->cp, sizeof(T) * (size_t)G->Nrb));
-    RCHK(launch_fill(s, G->cp2, sizeof(T) * (size_t)G->Nrb));
-    RCHK(launch_fill(s, pb->st, sizeof(CGState)));
+    RCHK(launch_fill(s, FillList{}
+                            .add(pb->x, sizeof(double) * (size_t)pb->g.N)
+                            .add(G->cx, sizeof(T) * (size_t)G->Nrb)
+                            .add(G->cp, sizeof(T) * (size_t)G->Nrb)
+                            .add(G->cp2, sizeof(T) * (size_t)G->Nrb)
+                            .add(pb->st, sizeof(CGState))));
     run_restart<T>(s, solo_plan(pb), 1, 1);
     RCHK(hipGetLastError());
     return PB_OK;

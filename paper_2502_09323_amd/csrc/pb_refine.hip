@@ -1096,8 +1096,7 @@ int pbi_refine_build(pb_problem* pb, const double* xyz, const double* rad, const
     unsigned long long* cnt64 = (unsigned long long*)pb->mem.get(sizeof(unsigned long long) * 8);
     int* bad = (int*)pb->mem.get(sizeof(int) * 2);
     if (!cnt64 || !bad) return pbi_fail(PB_ENOMEM, "refinement counters");
-    RCHK(launch_fill(s, cnt64, sizeof(unsigned long long) * 8));
-    RCHK(launch_fill(s, bad, sizeof(int) * 2));
+    RCHK(launch_fill(s, FillList{}.add(cnt64, sizeof(unsigned long long) * 8).add(bad, sizeof(int) * 2)));
     Cells cells{R->cells, {R->nc[0], R->nc[1], R->nc[2]}};
     k_cell_checks<<<nblk(ncell, 256), 256, 0, s>>>(cells, cl[0], cl[1], cl[2], ch[0], ch[1], ch[2], cnt64);
     RCHK(hipGetLastError());
@@ -1223,13 +1222,14 @@ int pbi_refine_build(pb_problem* pb, const double* xyz, const double* rad, const
     const size_t Nc = (size_t)gc.N, Nf = (size_t)gf.N;
     double** vc[6] = {&R->bc, &R->rc, &R->zc, &R->pc, &R->qc, &R->dc};
     double** vf[6] = {&R->bf, &R->rf, &R->zf, &R->pf, &R->qf, &R->df};
+    FillList fl;
     for (int v = 0; v < 6; ++v) {
         *vc[v] = (double*)pb->mem.get(sizeof(double) * Nc);
         *vf[v] = (double*)pb->mem.get(sizeof(double) * Nf);
         if (!*vc[v] || !*vf[v]) return pbi_fail(PB_ENOMEM, "refined solver vectors");
-        RCHK(launch_fill(s, *vc[v], sizeof(double) * Nc));
-        RCHK(launch_fill(s, *vf[v], sizeof(double) * Nf));
+        fl.add(*vc[v], sizeof(double) * Nc).add(*vf[v], sizeof(double) * Nf);
     }
+    RCHK(launch_fill(s, fl));
     std::vector<void*> tmp_dev;
     auto scatter = [&](const std::vector<int64_t>& idx, const std::vector<double>& val, double* dst) -> int {
         if (idx.empty()) return PB_OK;
@@ -1268,13 +1268,14 @@ int pbi_refine_build(pb_problem* pb, const double* xyz, const double* rad, const
         if (!R->Kc32 || !R->Kf32) return pbi_fail(PB_ENOMEM, "refined FP32 coefficients");
         float** wc[6] = {&R->xc32, &R->rc32, &R->zc32, &R->pc32, &R->qc32, &R->dc32};
         float** wf[6] = {&R->xf32, &R->rf32, &R->zf32, &R->pf32, &R->qf32, &R->df32};
+        FillList fl32;
         for (int v = 0; v < 6; ++v) {
             *wc[v] = (float*)pb->mem.get(sizeof(float) * Nc);
             *wf[v] = (float*)pb->mem.get(sizeof(float) * Nf);
             if (!*wc[v] || !*wf[v]) return pbi_fail(PB_ENOMEM, "refined FP32 solver vectors");
-            RCHK(launch_fill(s, *wc[v], sizeof(float) * Nc));
-            RCHK(launch_fill(s, *wf[v], sizeof(float) * Nf));
+            fl32.add(*wc[v], sizeof(float) * Nc).add(*wf[v], sizeof(float) * Nf);
         }
+        RCHK(launch_fill(s, fl32));
         k_to_f32<<<nblk(4 * gc.N, 256), 256, 0, s>>>(4 * gc.N, R->Kc, R->Kc32);
         k_to_f32<<<nblk(4 * gf.N, 256), 256, 0, s>>>(4 * gf.N, R->Kf, R->Kf32);
         k_to_f32<<<nblk(gc.N, 256), 256, 0, s>>>(gc.N, R->dc, R->dc32);
@@ -1407,13 +1408,19 @@ int pbi_refine_solve(pb_problem* pb, CGState* out)
         const int rc = pbi_mg_begin(pb, s);
         if (rc) return rc;
     }
-    RCHK(launch_fill(s, pb->x, sizeof(double) * (size_t)gc.N));
-    RCHK(launch_fill(s, fp->x, sizeof(double) * (size_t)gf.N));
+    FillList fl;
+    fl.add(pb->x, sizeof(double) * (size_t)gc.N).add(fp->x, sizeof(double) * (size_t)gf.N);
+    if (mixed)
+        fl.add(R->xc32, sizeof(float) * (size_t)gc.N).add(R->xf32, sizeof(float) * (size_t)gf.N);
+    else
+        fl.add(R->pc, sizeof(double) * (size_t)gc.N)
+            .add(R->pf, sizeof(double) * (size_t)gf.N)
+            .add(R->qc, sizeof(double) * (size_t)gc.N)
+            .add(R->qf, sizeof(double) * (size_t)gf.N);
+    RCHK(launch_fill(s, fl));
     k_state_init<<<1, 1, 0, s>>>(st);
     if (mixed) {
         // x32 = 0; r = b, z = D^-1 r from the first reliable update; p = z
-        RCHK(launch_fill(s, R->xc32, sizeof(float) * (size_t)gc.N));
-        RCHK(launch_fill(s, R->xf32, sizeof(float) * (size_t)gf.N));
         launch_reliable_update(s, pb, sp, 1, P.rtol * P.rtol, P.inner_rtol * P.inner_rtol, two_level);
         k_pupd<float><<<nb, 256, 0, s>>>(sp, two_level ? R->qc32 : R->zc32, two_level ? R->qf32 : R->zf32, R->pc32,
                                          R->pf32, st);
@@ -1422,10 +1429,6 @@ int pbi_refine_solve(pb_problem* pb, CGState* out)
         // and the norms; p = z
         RCHK(hipMemcpyAsync(R->rc, R->bc, sizeof(double) * (size_t)gc.N, hipMemcpyDeviceToDevice, s));
         RCHK(hipMemcpyAsync(R->rf, R->bf, sizeof(double) * (size_t)gf.N, hipMemcpyDeviceToDevice, s));
-        RCHK(launch_fill(s, R->pc, sizeof(double) * (size_t)gc.N));
-        RCHK(launch_fill(s, R->pf, sizeof(double) * (size_t)gf.N));
-        RCHK(launch_fill(s, R->qc, sizeof(double) * (size_t)gc.N));
-        RCHK(launch_fill(s, R->qf, sizeof(double) * (size_t)gf.N));
         k_update<double><<<nb, 256, 0, s>>>(sp, c64.x, c64.r, c64.z, c64.p, c64.q, c64.d, f64.x, f64.r, f64.z, f64.p,
                                             f64.q, f64.d, two_level ? kOmega : 1.0, R->part, nb, st);
         if (two_level) launch_two_level<double>(s, pb, gc, gf, sp, c64, f64, st);
