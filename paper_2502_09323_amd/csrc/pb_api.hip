@@ -731,6 +731,12 @@ int build_begin(pb_ctx* ctx, const pb_params* prm, int64_t na, const double* xyz
         pb->ahi[d] = hi[d];
     }
     pb->rmax = rmax;
+    double far2 = 0.0;
+    for (int64_t a = 0; a < na; ++a) {
+        const double dx = hx[4 * a] - pb->ctr[0], dy = hx[4 * a + 1] - pb->ctr[1], dz = hx[4 * a + 2] - pb->ctr[2];
+        far2 = std::max(far2, dx * dx + dy * dy + dz * dz);
+    }
+    pb->reach = std::sqrt(far2);
     const Atoms at = pbi_atoms(pb);
 
     // bins of edge >= R_max + h (and >= 2h) so that the 27 bins around a node or an edge end
@@ -848,7 +854,7 @@ int pbi_build_continue(pb_problem* pb)
     HIPCHK(launch_fill(s, FillList{}.add(pb->gb, sizeof(double) * N).add(pb->x, sizeof(double) * N)));
     if (prm->bc == PB_BC_DH && pb->na > 0) {
         DhInterp in;
-        const bool interp = prm->precision == PB_MIXED && dh_interp_plan(g, at, pb->alo, pb->ahi, pb->kD, &in);
+        const bool interp = prm->precision == PB_MIXED && dh_interp_plan(g, at, pb->alo, pb->ahi, pb->reach, pb->kD, &in);
         const DhSplit sp = interp ? in.sp : dh_split(g, at.n);
         T.dhpart = dalloc<double>(pb, (size_t)sp.ranges * sp.nbox, &rc);
         CK(rc);

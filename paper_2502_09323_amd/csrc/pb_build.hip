@@ -821,14 +821,20 @@ __global__ void __launch_bounds__(256) k_bc_dh_sum(Grid g, DhSplit sp, const dou
 // All atoms lie at least D from a face's plane, so the box value is an analytic function on the
 // face: a panel of half-length a, sampled at the n Chebyshev nodes of each axis, is interpolated
 // with an error of rho^-n, rho = D/a + sqrt((D/a)^2 + 1) (the nearest singularity lies D off the
-// plane).  What is interpolated is the value divided by exp(-kD r)/r of one charge at the atoms'
-// centre, which is flat where the value itself falls by orders of magnitude across a face.
+// plane), times the function's largest modulus on the ellipse of that rho, which rises by up to
+// exp(kD D) above the real values.  What is interpolated is the value divided by exp(-kD r)/r of one
+// charge at the atoms' centre, which is flat on a panel where the solute is compact.  Where it is long
+// against a Debye length, an atom's share of it is not: over a panel it falls by up to exp(2 kD x panel
+// length), and with degrees from D alone a rod of 580 A in 0.145 M salt was off by 1e-6 and in 1 M by
+// more than the values themselves.  The plan therefore forms that fall and takes shorter panels or more
+// samples for it, or declines.
 //
 // The mixed form's values come from samples that are FP64 sums (k_bc_dh), so they are closer to the
-// exact ones than the FP32 sums at every node that they replace: off by 3e-14 of the absolute-value
-// scale and less, against 1e-8 to 1e-7.  385^3, 60,000 atoms: 32,000 samples for 887,000 nodes, 2.4
-// ms in place of 15.2 (with FP32 sums at the samples 1.1 ms, but off by up to 1.5 times what the
-// nodes' own sums were).  The FP64 form keeps its sums at every node.
+// exact ones than the FP32 sums at every node that they replace (off by 1e-8 to 1e-7 of each node's
+// sum of absolute values): 1e-12 and less for globules, up to 6e-11 for rods, plates and scattered
+// clusters in 0 to 1 M salt.  385^3, 60,000 atoms: 38,000 samples for 887,000 nodes, 2.5 ms in place of
+// 15.2 (with FP32 sums at the samples 1.1 ms, but off by up to 1.5 times what the nodes' own sums
+// were).  The FP64 form keeps its sums at every node.
 
 // exp(-kD r) / r of a unit charge at the atoms' centre
 __device__ __forceinline__ double dh_centre(double kD, double w, double u, double v)
@@ -1310,53 +1316,140 @@ DhFaces dh_faces(const Grid& g)
     return fc;
 }
 
-bool dh_interp_plan(const Grid& g, const Atoms& at, const double* lo, const double* hi, double kD, DhInterp* out)
+// How much the scaled value of one atom, exp(-kD (r - r0)) r0 / r (r0: distance to the atoms' centre),
+// can rise on a panel's ellipse above its least on the panel, as a logarithm: the most over the panels of
+// face f and over 26 places on the atoms' bounding box, drawn in to the ball that holds all centres.
+// The value is taken at the middle, edges and corners of the panel and of its extension to the ellipse's
+// ends, and at the foot of the place.
+static double dh_variation(const DhPanels& pn, int f, const int* P, double D, double pw, const double (*place)[3],
+                           double kD)
+{
+    const int w = f >> 1, ax[2] = {w == 0 ? 1 : 0, w == 2 ? 1 : 2};
+    double half[2], ext[2], worst = 0.0;
+    for (int a = 0; a < 2; ++a) {
+        half[a] = pn.half[f][a] * pn.panels[f][a] / P[a];
+        ext[a] = std::sqrt(half[a] * half[a] + D * D);
+    }
+    for (int pu = 0; pu < P[0]; ++pu)
+        for (int pv = 0; pv < P[1]; ++pv) {
+            const double m[2] = {pn.lo[f][0] + half[0] * (2 * pu + 1), pn.lo[f][1] + half[1] * (2 * pv + 1)};
+            double x[18][2], r0[18];
+            for (int t = 0; t < 18; ++t) {
+                const double* e = t < 9 ? half : ext;
+                x[t][0] = m[0] + e[0] * (t % 3 - 1);
+                x[t][1] = m[1] + e[1] * (t / 3 % 3 - 1);
+                r0[t] = std::sqrt(pw * pw + x[t][0] * x[t][0] + x[t][1] * x[t][1]);
+            }
+            for (int c = 0; c < 26; ++c) {
+                const double *A = place[c], dw = pw - A[w], u = A[ax[0]], v = A[ax[1]];
+                double ehi = -1e300, elo = 1e300, rhi = 0.0, rlo = 1e300;
+                auto take = [&](double xu, double xv, double q, bool inside) {
+                    const double r = std::sqrt(dw * dw + (xu - u) * (xu - u) + (xv - v) * (xv - v));
+                    const double e = q - r, ratio = q / r;
+                    ehi = std::max(ehi, e);
+                    rhi = std::max(rhi, ratio);
+                    if (!inside) return;
+                    elo = std::min(elo, e);
+                    rlo = std::min(rlo, ratio);
+                };
+                for (int t = 0; t < 18; ++t) take(x[t][0], x[t][1], r0[t], t < 9);
+                const double fu = std::min(std::max(u, m[0] - ext[0]), m[0] + ext[0]);
+                const double fv = std::min(std::max(v, m[1] - ext[1]), m[1] + ext[1]);
+                take(fu, fv, std::sqrt(pw * pw + fu * fu + fv * fv), false);
+                worst = std::max(worst, kD * (ehi - elo) + std::log(rhi / rlo));
+            }
+        }
+    return worst;
+}
+
+bool dh_interp_plan(const Grid& g, const Atoms& at, const double* lo, const double* hi, double reach, double kD,
+                    DhInterp* out)
 {
     DhInterp d{};
     const DhFaces nodes = dh_faces(g);
     const double org[3] = {g.ox, g.oy, g.oz}, cen[3] = {at.cx, at.cy, at.cz};
     const int nn[3] = {g.nx, g.ny, g.nz};
-    int64_t total = 0;
+    double dist[6], pw[6], far2 = 0.0;
+    for (int c = 0; c < 3; ++c) {
+        const double o = org[c] + g.h * (double)g.off[c] - cen[c];
+        const double s = std::max(std::fabs(o), std::fabs(o + g.h * (double)(nn[c] - 1)));
+        far2 += s * s;
+    }
+    // a value of the charge at the centre that could not be divided by
+    if (!(kD * std::sqrt(far2) < 600.0)) return false;
     for (int f = 0; f < 6; ++f) {
         const int w = f >> 1, ax[2] = {w == 0 ? 1 : 0, w == 2 ? 1 : 2}, shift[2] = {w == 0 ? 0 : 1, w == 2 ? 1 : 0};
         const int cnt[2] = {nodes.U[f], nodes.V[f]};
         // distance of the atoms' centres to the face's plane
         const double plane = org[w] + g.h * (double)(((f & 1) ? nn[w] - 1 : 0) + g.off[w]);
-        const double D = (f & 1) ? plane - hi[w] : lo[w] - plane;
-        if (!(D > 0.0) || kD * D > 30.0) return false;
-        int S[2];
+        dist[f] = (f & 1) ? plane - hi[w] : lo[w] - plane;
+        pw[f] = plane - cen[w];
+        if (!(dist[f] > 0.0) || kD * dist[f] > 30.0) return false;
         for (int a = 0; a < 2; ++a) {
-            const double x0 = org[ax[a]] + g.h * (double)(shift[a] + g.off[ax[a]]) - cen[ax[a]];
-            const double len = g.h * (double)(cnt[a] - 1);
-            // the fewest panels whose degree stays within kDhMaxDegree; rho^-n = e^(-kD D) 1e-10
-            int P = 1, n = 0;
-            for (;; ++P) {
-                const double q = 2.0 * D * P / std::max(len, g.h);
-                n = (int)std::ceil((23.03 + kD * D) / std::log(q + std::sqrt(q * q + 1.0)));
-                if (n <= kDhMaxDegree) break;
-                if ((int64_t)(P + 1) * kDhMaxDegree > 2 * (int64_t)cnt[a]) return false;
-            }
-            n = std::max(n, 4);
-            d.pn.n[f][a] = n;
-            d.pn.panels[f][a] = P;
-            d.pn.lo[f][a] = x0;
-            d.pn.half[f][a] = 0.5 * std::max(len, g.h) / P;
+            d.pn.panels[f][a] = 1;
+            d.pn.lo[f][a] = org[ax[a]] + g.h * (double)(shift[a] + g.off[ax[a]]) - cen[ax[a]];
+            d.pn.half[f][a] = 0.5 * std::max(g.h * (double)(cnt[a] - 1), g.h);
             d.pn.nodes[f][a] = cnt[a];
-            S[a] = P * n;
         }
-        if (S[1] > kDhMaxRow) return false;
-        d.fc.U[f] = S[0];
-        d.fc.V[f] = S[1];
-        d.fc.base[f] = total;
-        total += (int64_t)S[0] * S[1];
+    }
+    double place[26][3];
+    for (int c = 0, t = 0; t < 27; ++t) {
+        if (t == 13) continue;
+        const int sg[3] = {t / 9 - 1, t / 3 % 3 - 1, t % 3 - 1};
+        double n2 = 0.0;
+        for (int k = 0; k < 3; ++k) {
+            place[c][k] = 0.5 * (hi[k] - lo[k]) * sg[k];
+            n2 += place[c][k] * place[c][k];
+        }
+        if (n2 > reach * reach)
+            for (int k = 0; k < 3; ++k) place[c][k] *= reach / std::sqrt(n2);
+        ++c;
+    }
+    d.sp = dh_split(g, at.n);
+    const int64_t nbox = d.sp.nbox;
+    int64_t total = 0;
+    // first without the variation, which takes longer than all the rest: problems too small stop there
+    for (int pass = 0; pass < 2; ++pass) {
+        total = 0;
+        for (int f = 0; f < 6; ++f) {
+            const double D = dist[f];
+            const int* cnt = d.pn.nodes[f];
+            int P[2] = {d.pn.panels[f][0], d.pn.panels[f][1]}, n[2];
+            // samples per panel: rho^-n = e^(-kD D) times 1e-10, or 1e-7 e^-V
+            auto degrees = [&](double V) {
+                for (int a = 0; a < 2; ++a) {
+                    const double q = D * P[a] / (d.pn.half[f][a] * d.pn.panels[f][a]);
+                    const double want = (std::max(23.03, 16.12 + V) + kD * D) / std::log(q + std::sqrt(q * q + 1.0));
+                    n[a] = std::max(4, (int)std::ceil(std::min(want, 1e6)));
+                }
+            };
+            // the fewest panels whose degrees stay within kDhMaxDegree
+            for (;;) {
+                degrees(0.0);
+                if (pass && std::max(n[0], n[1]) <= kDhMaxDegree)
+                    degrees(dh_variation(d.pn, f, P, D, pw[f], place, kD));
+                const int a = n[0] >= n[1] ? 0 : 1;
+                if (n[a] <= kDhMaxDegree) break;
+                P[a] += pass ? std::max(1, P[a] / 4) : 1;
+                if ((int64_t)P[a] * kDhMaxDegree > 2 * (int64_t)cnt[a]) return false;
+            }
+            for (int a = 0; a < 2; ++a) {
+                d.pn.half[f][a] *= (double)d.pn.panels[f][a] / P[a];
+                d.pn.panels[f][a] = P[a];
+                d.pn.n[f][a] = n[a];
+            }
+            d.fc.U[f] = P[0] * n[0];
+            d.fc.V[f] = P[1] * n[1];
+            if (d.fc.V[f] > kDhMaxRow) return false;
+            d.fc.base[f] = total;
+            total += (int64_t)d.fc.U[f] * d.fc.V[f];
+            // a sample's pairs in FP64 take about 2.5 times a node's in FP32: worth it from 3e8 FP32
+            // pairs saved on (129^3, 3000 atoms, 1.8e8 saved: 150 us against 139 us at every node; 257^3,
+            // 18,000 atoms: 0.73 against 2.27 ms; 385^3, 60,000 atoms: 2.4 against 15.2 ms)
+            if ((double)at.n * ((double)nbox - 2.5 * (double)total) < 3e8) return false;
+        }
     }
     dh_patches(d.fc);
-    d.sp = dh_split(g, at.n);
-    // a sample's pairs in FP64 take about 2.5 times a node's in FP32: worth it from 3e8 FP32
-    // pairs saved on (129^3, 3000 atoms, 1.8e8 saved: 150 us against 139 us at every node; 257^3,
-    // 18,000 atoms: 0.73 against 2.27 ms; 385^3, 60,000 atoms: 2.4 against 15.2 ms)
-    const int64_t nbox = d.sp.nbox;
-    if ((double)at.n * ((double)nbox - 2.5 * (double)total) < 3e8) return false;
     // enough blocks (of 2048 samples each at most) for the device; the partial sums take no more
     // room than those of all box nodes
     const int chunks = std::max(1, (at.n + 255) / 256);

@@ -205,6 +205,7 @@ struct pb_problem {
     double lB, kD;
     double ctr[3] = {0.0, 0.0, 0.0};   // centre of the atoms' bounding box (Atoms::cx, cy, cz)
     double alo[3] = {0.0, 0.0, 0.0}, ahi[3] = {0.0, 0.0, 0.0}, rmax = 0.0;   // that box and the largest radius
+    double reach = 0.0;                // the farthest atom centre's distance from the box's centre
     DevAlloc mem;
     // inputs
     double* xyzr = nullptr;

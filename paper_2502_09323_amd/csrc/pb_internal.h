@@ -216,8 +216,10 @@ struct DhInterp {
     DhFaces fc;    // the faces as arrays of samples
     DhSplit sp;    // atom ranges; nbox: samples
 };
-// lo, hi: the atoms' bounding box.  False: the sum at every box node is the better way.
-bool dh_interp_plan(const Grid& g, const Atoms& at, const double* lo, const double* hi, double kD, DhInterp* out);
+// lo, hi: the atoms' bounding box; reach: the farthest centre's distance from its middle.  False: the
+// sum at every box node is the better way.
+bool dh_interp_plan(const Grid& g, const Atoms& at, const double* lo, const double* hi, double reach, double kD,
+                    DhInterp* out);
 // part holds d.sp.ranges * d.sp.nbox doubles
 hipError_t launch_bc_dh_interp(hipStream_t s, const Grid& g, const Atoms& at, double kD, double eps_out,
                                const DhInterp& d, double* part, double* gb);
