@@ -162,11 +162,11 @@ int run_cg(pb_problem* pb, const CGBufs<T>& B, int max_iter, bool mixed, CGState
             if (pb->small.items) {
                 HIPCHK(launch_cg_small<T>(s, pb->g, pb->small, B, pb->cf, t));
                 if (sample) HIPCHK(hipEventRecord(e1, s));
-                if (t == n - 1) HIPCHK(launch_cg_tail(s, B.part, pb->small.items, 5 * pb->small.items, B.st));
+                if (t == n - 1) HIPCHK(launch_cg_tail(s, B.part, pb->small.items, 5 * pb->small.items, t & 1, B.st));
             } else {
                 HIPCHK(launch_cg_iter<T>(s, pb->g, pb->ts, B, pb->cf));
                 if (sample) HIPCHK(hipEventRecord(e1, s));
-                HIPCHK(launch_cg_tail(s, B.part, B.nb, 0, B.st));
+                HIPCHK(launch_cg_tail(s, B.part, B.nb, 0, -1, B.st));
             }
             if (sample) {
                 HIPCHK(hipEventRecord(e2, s));

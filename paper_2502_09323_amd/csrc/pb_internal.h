@@ -127,6 +127,7 @@ struct CGState {
     int ru;            // 1 while a reliable update is in progress
     int n_ru;          // reliable updates done
     int chunk0;        // small grids: iter_count at the start of the chunk of launches
+    int step_status[2];   // small grids: the status after launch t of the chunk, in slot t & 1
 };
 
 struct TileShape {     // tiling of the interior for the stencil kernel
@@ -273,8 +274,9 @@ hipError_t launch_cg_init(hipStream_t s, const Grid& g, const CGBufs<T>& B, Coef
 hipError_t launch_cg_fin(hipStream_t s, const double* part, int nb, CGState* st, double rtol2);
 template <typename T>
 hipError_t launch_cg_iter(hipStream_t s, const Grid& g, const TileShape& ts, const CGBufs<T>& B, Coef c);
-// alt: 0, or how far the sums of odd iterations lie behind those of even ones
-hipError_t launch_cg_tail(hipStream_t s, const double* part, int nb, int alt, CGState* st);
+// alt: 0, or how far the sums of odd iterations lie behind those of even ones; last: -1, or the slot of
+// step_status that the launch before wrote
+hipError_t launch_cg_tail(hipStream_t s, const double* part, int nb, int alt, int last, CGState* st);
 // Small grids: one launch per iteration, which closes the iteration before it itself.  B.part holds
 // two sets of 5 * items partial sums, by the parity of the iteration; t: position in its chunk (at 0
 // the scalars and the iteration's number come from the state).

@@ -335,7 +335,7 @@ __device__ __forceinline__ Step next_step(const double (&v)[5], double stop2, in
     return s;
 }
 
-// the state after iteration it (one thread)
+// the state after iteration it but for the status (one thread)
 __device__ __forceinline__ void write_step(const Step& s, const double (&v)[5], int it, CGState* st)
 {
     st->iter_count = it + 1;
@@ -346,10 +346,7 @@ __device__ __forceinline__ void write_step(const Step& s, const double (&v)[5], 
         st->beta = s.beta;
         st->gamma = v[1];
     }
-    if (s.status != 0) {
-        st->status = s.status;
-        st->iters = it;
-    }
+    if (s.status != 0) st->iters = it;
 }
 
 // one block: reduce the iteration's partial sums and set the scalars of the next iteration
@@ -380,11 +377,17 @@ __device__ __forceinline__ void tail_body(const double* __restrict__ part, int n
     const int it = st->iter_count;
     const Step s = next_step(v, st->stop2, st->stop_status);
     write_step(s, v, it, st);
+    if (s.status != 0) st->status = s.status;
 }
 
-// alt: distance of the odd iterations' partial sums from the even ones' (0: one set)
-__global__ void __launch_bounds__(256) k_cg_tail(const double* __restrict__ part, int nb, int alt, CGState* st)
+// alt: distance of the odd iterations' partial sums from the even ones' (0: one set); last: the slot of
+// st->step_status that the chunk's last launch wrote, or -1
+__global__ void __launch_bounds__(256) k_cg_tail(const double* __restrict__ part, int nb, int alt, int last, CGState* st)
 {
+    if (last >= 0 && st->step_status[last] != 0) {
+        if (threadIdx.x == 0) st->status = st->step_status[last];
+        return;
+    }
     tail_body(part + (st->iter_count & 1) * alt, nb, st);
 }
 
@@ -396,8 +399,11 @@ __global__ void __launch_bounds__(256) k_cg_tail(const double* __restrict__ part
 // reduces the partial sums of the iteration before (two sets, by parity) and takes the scalar step
 // itself.  All blocks reduce the same numbers in the same order, so they agree; block 0 writes the
 // state.  The first launch of a chunk takes its scalars and its number from the state, which no
-// block of it changes but for chunk0, and the chunk's last iteration is closed by k_cg_tail.  Same
-// recurrences as iter_body; the sums in another order.
+// block of it changes but for chunk0, and the chunk's last iteration is closed by k_cg_tail.  Blocks
+// of one launch are not ordered, so no wave may read what block 0 writes: whether the iteration has
+// stopped goes through two slots, launch t of a chunk reading the one of t - 1 (all its waves the same
+// value) and writing its own, and k_cg_tail moves the last one to the status.  Same recurrences as
+// iter_body; the sums in another order.
 // Per iteration in us (FP64 | mixed, before -> now): 33^3 14.8 -> 6.9 | 14.2 -> 7.8, 65^3 15.0 ->
 // 8.5 | 13.9 -> 8.0, 97^3 25.3 -> 17.7 | 17.6 -> 13.9, 129^3 44.9 -> 34.3 | 30.1 -> 25.5, 145^3
 // 65.3 -> 52.1 | 43.5 -> 39.1.  At 65^3 what is left is launch, one round of loads, two block
@@ -453,9 +459,15 @@ __global__ void __launch_bounds__(SM_T) k_cg_small(Grid g, SmallShape ss, CGBufs
     __shared__ int stop;
     __shared__ T sp[SM_X + 2][SM_Y + 2][34];
     CGState* st = B.st;
-    if (st->status != 0) return;
+    const int tid = (int)threadIdx.x;
+    int* const mine = &st->step_status[t0 & 1];
+    const int before = t0 == 0 ? st->status : st->step_status[(t0 & 1) ^ 1];
+    if (before != 0) {
+        if (blockIdx.x == 0 && tid == 0) *mine = before;
+        return;
+    }
     const int it = t0 == 0 ? st->iter_count : st->chunk0 + t0;
-    const int nw = it & 1, od = nw ^ 1, tid = (int)threadIdx.x;
+    const int nw = it & 1, od = nw ^ 1;
     const T kin = (T)cf.kin, kout = (T)cf.kout, mass = (T)cf.mass;
     // one eighth of the tiles per XCD (no tile costs more than another here; runs of 4, 16 and 64 tiles:
     // 97^3 FP64 18.9, 18.0, 17.8 us, eighths 17.8)
@@ -524,7 +536,10 @@ __global__ void __launch_bounds__(SM_T) k_cg_small(Grid g, SmallShape ss, CGBufs
     if (t0 == 0) {
         aT = (T)st->alpha;
         bT = (T)st->beta;
-        if (blockIdx.x == 0 && tid == 0) st->chunk0 = it;
+        if (blockIdx.x == 0 && tid == 0) {
+            st->chunk0 = it;
+            *mine = 0;
+        }
     } else {
         const double* part = B.part + (int64_t)od * 5 * ss.items;
         double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
@@ -541,7 +556,10 @@ __global__ void __launch_bounds__(SM_T) k_cg_small(Grid g, SmallShape ss, CGBufs
                                           __builtin_amdgcn_readlane(__double2loint(r), 8 * u + 7));
             if (tid == 0) {
                 const Step s = next_step(tot, st->stop2, st->stop_status);
-                if (blockIdx.x == 0) write_step(s, tot, it - 1, st);
+                if (blockIdx.x == 0) {
+                    write_step(s, tot, it - 1, st);
+                    *mine = s.status;
+                }
                 step[0] = s.alpha;
                 step[1] = s.beta;
                 stop = s.status;
@@ -1000,9 +1018,9 @@ template hipError_t launch_cg_small<double>(hipStream_t, const Grid&, const Smal
                                             int);
 template hipError_t launch_cg_small<float>(hipStream_t, const Grid&, const SmallShape&, const CGBufs<float>&, Coef, int);
 
-hipError_t launch_cg_tail(hipStream_t s, const double* part, int nb, int alt, CGState* st)
+hipError_t launch_cg_tail(hipStream_t s, const double* part, int nb, int alt, int last, CGState* st)
 {
-    k_cg_tail<<<1, 256, 0, s>>>(part, nb, alt, st);
+    k_cg_tail<<<1, 256, 0, s>>>(part, nb, alt, last, st);
     return hipGetLastError();
 }
 
