@@ -313,8 +313,10 @@ int pb_copy_cut(const pb_problem* pb, int64_t* key, double* alpha, double* rp, d
 /* Average duration in milliseconds of `reps` back-to-back launches of the fused stencil
  * kernel of the problem's CG (one launch = one operator application plus the
  * search-direction update and the p.Ap partial sums), FP64 or FP32 (fp32 != 0), timed with
- * HIP events on the problem's stream.  It overwrites the solver state: call pb_solve again
- * before pb_energy. */
+ * HIP events on the problem's stream.  For a Jacobi problem on a small grid with tile_planes 0
+ * that is the kernel whose launch is a whole iteration, without the share of it that closes
+ * the iteration before (a few microseconds); a multigrid problem's is the Jacobi one.  It
+ * overwrites the solver state: call pb_solve again before pb_energy. */
 int pb_time_stencil(pb_problem* pb, int32_t reps, int32_t fp32, double* avg_ms);
 
 /* Turn on (1) or off (0) sampled HIP-event timing of the CG kernels: every 8th iteration's
@@ -322,7 +324,8 @@ int pb_time_stencil(pb_problem* pb, int32_t reps, int32_t fp32, double* avg_ms);
 int pb_ctx_set_profiling(pb_ctx* ctx, int on);
 
 /* Average durations (ms) of the sampled stencil and update launches of the last pb_solve
- * (only iterations that did work are counted), and the number of samples.  For a
+ * (only iterations that did work are counted), and the number of samples.  Where one launch
+ * is a whole iteration (Jacobi, a small grid, tile_planes 0): that launch, and 0.  For a
  * PB_PRECOND_MG solve with more than one level: the first level-0 black half-sweep after the
  * coarse correction, and the whole V-cycle. */
 int pb_get_profile(const pb_problem* pb, double* stencil_ms_avg, double* update_ms_avg, int32_t* samples);

@@ -152,11 +152,11 @@ int run_cg(pb_problem* pb, const CGBufs<T>& B, int max_iter, bool mixed, CGState
         for (int t = 0; t < n; ++t) {
             const int it = launched + t;
             const bool sample = prof && (it % 8 == 0) && evs.size() < 3 * 256;
-            hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr;
+            hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr;   // e2: null where one launch is the iteration
             if (sample) {
                 HIPCHK(hipEventCreate(&e0));
                 HIPCHK(hipEventCreate(&e1));
-                HIPCHK(hipEventCreate(&e2));
+                if (!pb->small.items) HIPCHK(hipEventCreate(&e2));
                 HIPCHK(hipEventRecord(e0, s));
             }
             if (pb->small.items) {
@@ -167,9 +167,9 @@ int run_cg(pb_problem* pb, const CGBufs<T>& B, int max_iter, bool mixed, CGState
                 HIPCHK(launch_cg_iter<T>(s, pb->g, pb->ts, B, pb->cf));
                 if (sample) HIPCHK(hipEventRecord(e1, s));
                 HIPCHK(launch_cg_tail(s, B.part, B.nb, 0, -1, B.st));
+                if (sample) HIPCHK(hipEventRecord(e2, s));
             }
             if (sample) {
-                HIPCHK(hipEventRecord(e2, s));
                 evs.push_back(e0);
                 evs.push_back(e1);
                 evs.push_back(e2);
@@ -214,13 +214,14 @@ int run_cg(pb_problem* pb, const CGBufs<T>& B, int max_iter, bool mixed, CGState
             if (ev_it[k] < done) {
                 float a = 0, b = 0;
                 HIPCHK(hipEventElapsedTime(&a, evs[3 * k], evs[3 * k + 1]));
-                HIPCHK(hipEventElapsedTime(&b, evs[3 * k + 1], evs[3 * k + 2]));
+                if (evs[3 * k + 2]) HIPCHK(hipEventElapsedTime(&b, evs[3 * k + 1], evs[3 * k + 2]));
                 ts += a;
                 tu += b;
                 ++n;
             }
         }
-        for (auto e : evs) (void)hipEventDestroy(e);
+        for (auto e : evs)
+            if (e) (void)hipEventDestroy(e);
         pb->prof_stencil_ms += ts;
         pb->prof_update_ms += tu;
         pb->prof_n += n;
@@ -1176,23 +1177,22 @@ int pb_time_stencil(pb_problem* pb, int32_t reps, int32_t fp32, double* avg_ms)
     HIPCHK(hipEventCreate(&b));
     pb->solved = false;
     const double rtol2 = pb->prm.rtol * pb->prm.rtol;
-    if (fp32) {
-        CGBufs<float> B = bufs<float>(pb);
-        HIPCHK(launch_cg_init<float>(s, pb->g, B, pb->cf, pb->rhs, nullptr));
+    auto time = [&](auto B, auto zero) -> int {
+        using T = decltype(zero);
+        // the kernel that this problem's solve runs (each launch as the first of a chunk)
+        auto launch = [&]() {
+            return pb->small.items ? launch_cg_small<T>(s, pb->g, pb->small, B, pb->cf, 0)
+                                   : launch_cg_iter<T>(s, pb->g, pb->ts, B, pb->cf);
+        };
+        HIPCHK(launch_cg_init<T>(s, pb->g, B, pb->cf, pb->rhs, nullptr));
         HIPCHK(launch_cg_fin(s, pb->part, pb->nb, pb->st, rtol2));
-        HIPCHK(launch_cg_iter<float>(s, pb->g, pb->ts, B, pb->cf));
+        HIPCHK(launch());
         HIPCHK(hipEventRecord(a, s));
-        for (int t = 0; t < reps; ++t) HIPCHK(launch_cg_iter<float>(s, pb->g, pb->ts, B, pb->cf));
+        for (int t = 0; t < reps; ++t) HIPCHK(launch());
         HIPCHK(hipEventRecord(b, s));
-    } else {
-        CGBufs<double> B = bufs<double>(pb);
-        HIPCHK(launch_cg_init<double>(s, pb->g, B, pb->cf, pb->rhs, nullptr));
-        HIPCHK(launch_cg_fin(s, pb->part, pb->nb, pb->st, rtol2));
-        HIPCHK(launch_cg_iter<double>(s, pb->g, pb->ts, B, pb->cf));
-        HIPCHK(hipEventRecord(a, s));
-        for (int t = 0; t < reps; ++t) HIPCHK(launch_cg_iter<double>(s, pb->g, pb->ts, B, pb->cf));
-        HIPCHK(hipEventRecord(b, s));
-    }
+        return PB_OK;
+    };
+    if ((rc = fp32 ? time(bufs<float>(pb), 0.0f) : time(bufs<double>(pb), 0.0))) return rc;
     HIPCHK(hipEventSynchronize(b));
     float ms = 0;
     HIPCHK(hipEventElapsedTime(&ms, a, b));
