@@ -1179,6 +1179,7 @@ inline unsigned nblk(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); 
 
 hipError_t launch_fill(hipStream_t s, FillList l)
 {
+    if (l.n > FillList::kMax) return hipErrorInvalidValue;
     int64_t blocks = 0;
     int m = 0;
     for (int q = 0; q < l.n; ++q) {

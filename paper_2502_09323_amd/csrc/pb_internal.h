@@ -231,17 +231,20 @@ hipError_t launch_lift(hipStream_t s, const Grid& g, const uint32_t* code, const
 hipError_t launch_mc_weights(hipStream_t s, const Grid& g, const uint32_t* code, const int* cutbase,
                              int64_t ncut, const int64_t* cutkey, const double* rp, double* wp);
 // Zero fill of up to kMax buffers (16-byte aligned) by one launch, a kernel (no memset nodes, so callers
-// may capture it in a graph).
+// may capture it in a graph).  A list that was given more fails as a whole (hipErrorInvalidValue).
 struct FillList {
     static constexpr int kMax = 24;
-    int n = 0;
+    int n = 0;             // buffers given
     void* p[kMax];
     int64_t bytes[kMax];
     int first[kMax + 1];   // first block of each buffer
     FillList& add(void* q, size_t b)
     {
-        p[n] = q;
-        bytes[n++] = (int64_t)b;
+        if (n < kMax) {
+            p[n] = q;
+            bytes[n] = (int64_t)b;
+        }
+        ++n;
         return *this;
     }
 };
