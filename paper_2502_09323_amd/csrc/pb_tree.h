@@ -22,7 +22,7 @@ struct TreeGeom {
     double side;       // edge of a box
     double ctr[3];     // centre of box 0 relative to the atoms' centre
     double rinv;       // 1 / (half-diagonal of a box)
-    double alo[3], ainv;   // low corner and 1 / edge of those bins
+    double alo[3], ainv;   // low corner, and 1 / edge of the curve's cells
 };
 
 struct TreePlan {
