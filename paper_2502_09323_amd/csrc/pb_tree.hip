@@ -775,6 +775,14 @@ bool tree_plan(const Grid& g, const Atoms& at, const double* lo, const double* h
     }
     if (B > kMaxSide) return false;
     G.side = g.h * (double)B;
+    // A box acts on a group by its expansion from about twice its half-diagonal on.  Where the balls fill
+    // little of the bounding box (an atom far from the rest), or the work space asks for large boxes, that
+    // distance and the group's own extent can take in most of the solute; the direct sum is the faster one
+    // from half of it on.  Direct sum and expansions in ms by that share: 0.28 2.20 and 1.64, 0.41 5.67
+    // and 4.28, 0.45 4.98 and 3.98, 0.56 2.13 and 2.39, 0.67 9.4 and 10.2, 0.95 1.59 and 3.18.
+    const double occupied = 0.5236 * std::min(vol, (double)at.n * 8.0 * rmax * rmax * rmax);
+    const double near = 1.74 * G.side + std::cbrt(kGroup * occupied / (double)at.n);
+    if (4.19 * near * near * near > 0.5 * occupied) return false;
     for (int d = 0; d < 3; ++d)
         G.ctr[d] = (org[d] - c[d]) + g.h * ((double)(G.c0[d] + g.off[d]) + 0.5 * (double)B);
     G.rinv = 1.0 / (0.5 * std::sqrt(3.0) * G.side * (1.0 + 1e-9));

@@ -2,7 +2,8 @@
 fill little of it.
 
 With profiling on, a read-back by box expansions reports no pairs of the direct kernel, and one by the
-direct sum all of them.  Thin sheets and hollow shells put the cut points of a box into planes and
+direct sum all of them; the direct sum also takes the shapes for which the boxes would be too large to
+gain anything (an atom far from the rest, a sheet across the lattice).  Thin sheets and hollow shells put the cut points of a box into planes and
 corners, the patterns for which a box's expansion is least exact.  Tolerance, relative to the sums of
 absolute values, as for the other shapes: 1e-13 (terms left out: at most 3e-13 of a box's own sum for
 plane patches, a fraction of the whole; a pair's squared distance is rounded to 2e-13 at the worst, for a
@@ -46,6 +47,11 @@ def box_grid(mol, h, pad=3.0, **kw):
 def case_sheet():
     mol = T.lattice_molecule(lambda p: np.abs(p[:, 2]) < 1.0, (110.0, 110.0, 3.0), 7)
     return mol, box_grid(mol, 0.4)
+
+
+def case_tilted_sheet():
+    mol = T.lattice_molecule(lambda p: np.abs(p @ np.array([0.8, 0.36, 0.48])) < 1.6, (80.0, 80.0, 80.0), 8)
+    return mol, box_grid(mol, 0.45)
 
 
 def case_hollow():
@@ -104,23 +110,21 @@ def case_far_outlier():
     return mol, box_grid(mol, 1.0)
 
 
-@pytest.mark.parametrize("case", [case_few_pairs])
+def case_outlier_of_a_small_globule():
+    mol = with_atoms(T.globule(28.5, 1), np.array([[800.0, 0.0, 0.0]]))
+    return mol, box_grid(mol, 0.5)
+
+
+@pytest.mark.parametrize("case", [case_few_pairs, case_far_outlier, case_outlier_of_a_small_globule, case_tilted_sheet])
 def test_direct_sum_runs(ctx, case):
     mol, grid = case()
-    pb = B.Problem(ctx, mol, grid)
-    assert pb.solve()["status"] == 0
-    got = pb.energy()
-    assert pb.energy_profile()["nbody_pairs"] == float(mol.n) * got["n_cut"]
-    pb.close()
-
-
-def test_far_outlier_is_quick(ctx):
-    """One atom far from the rest leaves the others in a few bins of the curve: a few milliseconds."""
-    mol, grid = case_far_outlier()
+    print(f"direct sum: {case.__name__}, {mol.n} atoms, grid {grid.n}", flush=True)
     pb = B.Problem(ctx, mol, grid)
     assert pb.solve()["status"] == 0
     pb.energy()
-    assert pb.energy()["t_energy_s"] < 0.1
+    got = pb.energy(per_atom=True)
+    assert pb.energy_profile()["nbody_pairs"] == float(mol.n) * got["n_cut"]
+    assert got["t_energy_s"] < 0.1      # a few milliseconds
     pb.close()
 
 
