@@ -347,7 +347,6 @@ struct Split {
     __device__ bool coarse() const { return (int)blockIdx.x < nbc; }
     __device__ int64_t n() const { return coarse() ? Nc : Nf; }
     __device__ int64_t first() const { return (coarse() ? blockIdx.x : blockIdx.x - nbc) * (int64_t)256 + threadIdx.x; }
-    __device__ int64_t end() const { return n(); }
     __device__ int64_t stride() const { return (coarse() ? nbc : (int)gridDim.x - nbc) * (int64_t)256; }
     __device__ const uint8_t* role() const { return coarse() ? rc : rf; }
 };
@@ -405,7 +404,7 @@ __global__ void __launch_bounds__(256) k_apply(Split sp, int64_t sxc, int64_t sy
     T* __restrict__ o = coarse ? A.oc : A.of;
     const int64_t N = sp.n(), sx = coarse ? sxc : sxf, sy = coarse ? syc : syf;
     double v[1] = {0.0};
-    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) {
+    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride()) {
         const int ro = role[e];
         if (!ro) {
             o[e] = (T)0;
@@ -707,7 +706,7 @@ __global__ void __launch_bounds__(256) k_update(Split sp, T* xc, T* rrc, T* zc, 
     const T* d = coarse ? dc : df;
     const T a = (T)st->alpha;
     double v[2] = {0.0, 0.0};
-    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) {
+    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride()) {
         if (role[e] != 1) continue;
         x[e] += a * p[e];
         const T rv = r[e] - a * q[e];
@@ -772,7 +771,7 @@ __global__ void __launch_bounds__(256) k_pupd(Split sp, const T* zc, const T* zf
     const T* z = sp.coarse() ? zc : zf;
     T* p = sp.coarse() ? pc : pf;
     const T b = (T)st->beta;
-    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) p[e] = role[e] == 1 ? z[e] + b * p[e] : (T)0;
+    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride()) p[e] = role[e] == 1 ? z[e] + b * p[e] : (T)0;
 }
 
 // ---- two-level preconditioner ----------------------------------------------------------------
@@ -846,12 +845,12 @@ __global__ void __launch_bounds__(256) k_prol(Split sp, Grid gf, Grid gc, const 
     if (stopped(st)) return;
     const uint8_t* __restrict__ role = sp.role();
     if (sp.coarse()) {
-        for (int64_t e = sp.first(); e < sp.end(); e += sp.stride())
+        for (int64_t e = sp.first(); e < sp.n(); e += sp.stride())
             if (role[e] == 1) zc[e] += eH[e];
         return;
     }
     const int64_t gx = (int64_t)gc.ny * gc.S, gy = gc.S;
-    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) {
+    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride()) {
         if (role[e] != 1) continue;
         int i, j, k;
         decode(gf, e, i, j, k);
@@ -878,7 +877,7 @@ __global__ void __launch_bounds__(256) k_fold(Split sp, double* xc, float* dc, d
     double* x = sp.coarse() ? xc : xf;
     float* d = sp.coarse() ? dc : df;
     const uint8_t* role = sp.role();
-    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride())
+    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride())
         if (role[e] == 1) {
             x[e] += (double)d[e];
             d[e] = 0.0f;
@@ -896,7 +895,7 @@ __global__ void __launch_bounds__(256) k_true_res(Split sp, const double* bc, co
     const double* q = coarse ? qc : qf;
     double* r = coarse ? rc : rf;
     double v[1] = {0.0};
-    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) {
+    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride()) {
         const double rv = role[e] == 1 ? b[e] - q[e] : 0.0;
         r[e] = rv;
         v[0] += rv * rv;
@@ -918,7 +917,7 @@ __global__ void __launch_bounds__(256) k_replace(Split sp, const double* r64c, f
     float* z = coarse ? zc : zf;
     const float* d = coarse ? dc : df;
     double v[2] = {0.0, 0.0};
-    for (int64_t e = sp.first(); e < sp.end(); e += sp.stride()) {
+    for (int64_t e = sp.first(); e < sp.n(); e += sp.stride()) {
         const float rv = role[e] == 1 ? (float)r64[e] : 0.0f;
         const float zv = d[e] * rv;
         r[e] = rv;
