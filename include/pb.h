@@ -88,7 +88,9 @@ typedef struct {
     int32_t precision;      /* PB_FP64, or PB_MIXED: FP32 coefficients, vectors and CG with
                                FP64 reliable updates (true residual, solution accumulation);
                                the Debye-Hueckel box values then use FP32 exponentials and
-                               inverse distances with FP64 sums */
+                               inverse distances with FP64 sums, or, on large problems, are
+                               interpolated from FP64 sums at fewer points (closer to the
+                               exact values than the former) */
     double rtol;            /* stop when ||b - A x||_2 <= rtol ||b||_2 (FP64 path: CG
                                recursive residual; mixed: the FP64 true residual) */
     double inner_rtol;      /* PB_MIXED: reliable-update factor: the FP32 recursive residual
@@ -226,7 +228,8 @@ int pb_energy(pb_problem* pb, pb_energy_out* out, double* phi_reac_per_atom);
  * pb_energy_noalloc_limit() bytes (128 MiB), which every device the library runs on holds
  * until the process ends; its address is taken when the first context on the device is
  * created.  When the N-body sum in pb_energy's chunking does not fit, fewer chunks are used
- * (only the order of the FP64 additions changes).  The energies go to *out, the reaction
+ * (only the order of the FP64 additions changes), and box expansions take larger boxes or give
+ * way to the direct sum (the same sums to their rounding).  The energies go to *out, the reaction
  * potentials (kT/e, optional) to the caller's host array phi_reac_per_atom[n_atoms]; the
  * call returns when they are there.  Unlike pb_energy it leaves nothing with the problem, so
  * pb_copy_cut's F and phip stay those of the last pb_energy.  Every call on one device shares
@@ -415,8 +418,8 @@ int pb_server_profile(const pb_server* srv, double* stencil_ms_total, double* st
 /* The same for the multigrid requests: for every iteration of the batched multigrid chunks
  * (and the first iteration of every chunk of a request run alone) in which at least one
  * request iterated, the HIP-event time (ms) of the level-0 black half-sweep after the coarse
- * correction and its algorithmic bytes (10 per interior unknown of the requests that
- * iterated: in the red-black layout x of the other colour, b, 1/D and the node codes of the
+ * correction and its algorithmic bytes (8 per interior unknown of the requests that
+ * iterated: in the red-black layout x of the other colour, b and the node codes of the
  * swept colour read, x of the swept colour written), the time of the whole
  * V-cycle, and the number of samples. */
 int pb_server_profile_mg(const pb_server* srv, double* sweep_ms_total, double* sweep_bytes_total,
@@ -429,8 +432,9 @@ int pb_server_profile_mg(const pb_server* srv, double* sweep_ms_total, double* s
 int pb_server_profile_mg_apply(const pb_server* srv, double* ms_total, double* bytes_total, int64_t* launches);
 
 /* With profiling on in build_ctx: the HIP-event time (ms) of the energy N-body kernel summed
- * over every request read back, the pairs (n_atoms * n_cut) summed likewise, and the number
- * of such read-backs. */
+ * over every request read back by the direct sum (not by box expansions, see
+ * pb_get_energy_profile), the pairs (n_atoms * n_cut) summed likewise, and the number of such
+ * read-backs. */
 int pb_server_profile_energy(const pb_server* srv, double* nbody_ms_total, double* pairs_total, int64_t* calls);
 
 /* Wait for the device, release every resident problem and the server. */
